@@ -92,22 +92,11 @@ struct Draw53 {
 // Species stream: 32-bit uniforms in [0, 1), four per Philox call.
 struct Draw32 {
   uint32_t k0, k1, sid, tet, win, call;
-  uint32_t w0, w1, w2, w3;
+  uint32_t w0, w1, w2, w3;  // the call's words, the next one first
   int pos;
   __device__ Draw32(uint32_t key0, uint32_t key1, uint32_t stream, uint32_t t, uint32_t w)
       : k0(key0), k1(key1), sid(stream), tet(t), win(w), call(0), w0(0), w1(0), w2(0), w3(0),
         pos(4) {}
-  // Computes the stream's first Philox call up front, so that every item of a
-  // wave refills at the same program point (draw values are unchanged).
-  __device__ __forceinline__ void prime() {
-    w0 = call;
-    w1 = sid;
-    w2 = tet;
-    w3 = win;
-    philox4x32_10(w0, w1, w2, w3, k0, k1);
-    ++call;
-    pos = 0;
-  }
   // The stream's next Philox call (all four words unused).
   __device__ __forceinline__ void refill() {
     w0 = call;
@@ -121,7 +110,10 @@ struct Draw32 {
   // The next 32-bit word of the stream, and the uniform w 2^-32 it stands for.
   __device__ __forceinline__ uint32_t word() {
     if (pos == 4) refill();
-    const uint32_t w = pos == 0 ? w0 : (pos == 1 ? w1 : (pos == 2 ? w2 : w3));
+    const uint32_t w = w0;  // the words move up: a choice by pos is a branch per word
+    w0 = w1;
+    w1 = w2;
+    w2 = w3;
     ++pos;
     return w;
   }
@@ -185,22 +177,41 @@ struct ReciprocalTable {
 };
 __constant__ constexpr ReciprocalTable kRecip{};
 
-__device__ long long binom_core(long long m, double p, Draw32& st) {
+// Steps of the search per pass of its loop.  A step taken alone waits for its
+// own scalar load of the reciprocal (one load and one wait per pmf term) and
+// tests for the end; eight share one 64-byte scalar load, one wait and one
+// test.  Running past the end is harmless: the cdf does not fall (terms past
+// k = c are zero), so the answer is the number of cdf values that u reaches,
+// counted term by term and capped at c.  Against single steps: a window of the
+// 112k-tet dendrite (counts near 1000, about 100 terms a search) 915 -> 600 us,
+// of the 1M-tet one (counts near 110) 258 -> 247 us.
+constexpr int kSearchSteps = 8;
+static_assert(1000 % kSearchSteps == 0, "a pass never reads past the reciprocals");
+
+template <typename I>
+__device__ __forceinline__ I binom_core(I m, double p, Draw32& st) {
   const double q = 1.0 - p;
   const double r = p / q;
-  long long total = 0;
+  I total = 0;
   while (m > 0) {
     const int c = m < 1000 ? (int)m : 1000;
     const double u = st.u();
     double f = pow_int(q, c);
     double F = f;
     int k = 0;
-    while (u >= F && k < c) {
-      f = ((f * r) * (double)(c - k)) * kRecip.v[k];
-      k = k + 1;
-      F = F + f;
+    double left = (double)c;  // c - k of the next term
+    for (int j = 0; u >= F && j < c; j += kSearchSteps) {
+#pragma unroll
+      for (int s = 0; s < kSearchSteps; ++s) {
+        k += u >= F ? 1 : 0;
+        f = ((f * r) * left) * kRecip.v[j + s];
+        left = left - 1.0;
+        F = F + f;
+      }
     }
-    total += k;
+    // a pass that reached c counted the steps past it too when u stayed above
+    // the whole sum, and not the last comparison otherwise: both end at c
+    total += k < c ? k : c;
     m -= c;
   }
   return total;
@@ -208,11 +219,12 @@ __device__ long long binom_core(long long m, double p, Draw32& st) {
 
 // One code path for both sides of 1/2 (the complement is taken by flipping),
 // so that lanes of a wave with different p do not run two copies.
-__device__ __forceinline__ long long binom(long long m, double p, Draw32& st) {
+template <typename I>
+__device__ __forceinline__ I binom(I m, double p, Draw32& st) {
   if (m <= 0 || !(p > 0.0)) return 0;
   if (p >= 1.0) return m;
   const bool flip = p > 0.5;
-  const long long k = binom_core(m, flip ? 1.0 - p : p, st);
+  const I k = binom_core<I>(m, flip ? 1.0 - p : p, st);
   return flip ? m - k : k;
 }
 
@@ -498,18 +510,18 @@ __device__ ItemMoves item_round(uint32_t key0, uint32_t key1, uint32_t window, c
     Draw32 st(key0, key1, 1u + (uint32_t)it.sp, tet, window);
     const double fl = floor(it.nbar);
     const double frac = it.nbar - fl;
-    long long m = (long long)fl;
+    int m = (int)fl;  // counts are int32
     uint32_t used = 0;  // words taken before the face draws
     if (frac > 0.0) {
       if (st.u() < frac) m += 1;
       used = 1;
     }
     const double p = item_p(V, it.sp, it.ln);
-    long long trials = 0;
+    int trials = 0;
     if (m > 0 && p > 0.0) {
       if (m <= kSmallM) {
         trials = m;
-        walked = m > (long long)it.npost;  // the cap may bind mid-walk
+        walked = m > it.npost;  // the cap may bind mid-walk
       } else {
         // the multinomial over the faces and staying, one binomial per stage
         // from one call site, in stream order on this lane: stage k <= last
@@ -521,8 +533,8 @@ __device__ ItemMoves item_round(uint32_t key0, uint32_t key1, uint32_t window, c
         // Bin(rest, s_k / (1 - cum_{k-1})), the last face the rest).
         const int last = last_face(V.nbr[it.ln]);
         const double2 g0 = V.geo0[it.ln], g1 = V.geo1[it.ln];
-        const long long npost = (long long)it.npost;
-        long long rest = m, n = 0;
+        const int npost = it.npost;
+        int rest = m, n = 0;
         double prev = 0.0;
         bool capped = false;
         int end = last;
@@ -538,7 +550,7 @@ __device__ ItemMoves item_round(uint32_t key0, uint32_t key1, uint32_t window, c
           } else {
             qq = (cum - prev) / (1.0 - prev);
           }
-          const long long k = binom(rest, qq, st);
+          const int k = binom<int>(rest, qq, st);
           X.face[f][lane] = (uint32_t)k;
           rest -= k;
           prev = cum;
@@ -590,10 +602,10 @@ __device__ ItemMoves item_round(uint32_t key0, uint32_t key1, uint32_t window, c
       item_thresholds(V, it.ln, p, th, full);
 #pragma unroll
       for (int k = 0; k < 4; ++k) X.face[k][lane] = 0u;
-      long long n = 0;
-      for (long long j = 0; j < trials; ++j) {
+      int n = 0;
+      for (int j = 0; j < trials; ++j) {
         const uint32_t w = st.word();
-        if (draw_leaves(w, th[3], full) && n < (long long)it.npost) {
+        if (draw_leaves(w, th[3], full) && n < it.npost) {
           X.face[draw_face(w, th[0], th[1], th[2], full)][lane] += 1u;
           ++n;
         }
@@ -1590,7 +1602,7 @@ __global__ void selftest_binom_kernel(uint32_t key0, uint32_t key1, uint32_t str
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n) return;
   Draw32 st(key0, key1, stream_id, (uint32_t)j, window);
-  out[j] = binom(m, p, st);
+  out[j] = binom<long long>(m, p, st);
 }
 
 __global__ void copy_kernel(const int4* __restrict__ src, int4* __restrict__ dst, int64_t n16) {
