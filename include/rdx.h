@@ -217,16 +217,14 @@ rdx_status rdx_setup_geometry(const rdx_mesh* mesh, const rdx_model* model, doub
                               double* tau);
 
 /* Per-kernel device time, measured with HIP events recorded on the launch
- * stream around every window's two kernels while timing is enabled: the
- * detect kernel (propensities and first SSA waiting time of every tet; lists
- * the tets with an event in the window) and the main kernel (diffusion of
- * every other tet, and the full SSA window and diffusion of the listed tets
- * in blocks of their own).  Timing adds three event records per window and
- * plain launches; it is off by default. */
+ * stream around every window's kernel while timing is enabled.  One kernel
+ * lists the tets with an event in the window, runs their SSA and diffuses
+ * every tet: its duration is main_ms, and detect_ms is zero.  Timing adds two
+ * event records per window and plain launches; it is off by default. */
 typedef struct rdx_kernel_times {
   int64_t windows;        /* windows timed since the last reset */
-  double detect_ms;       /* summed duration of the detect kernel */
-  double main_ms;         /* summed duration of the main kernel */
+  double detect_ms;       /* 0: the listing is part of the window kernel */
+  double main_ms;         /* summed duration of the window kernel */
 } rdx_kernel_times;
 
 rdx_status rdx_set_kernel_timing(rdx_sim* sim, int enable);
@@ -241,28 +239,22 @@ rdx_status rdx_get_kernel_times(rdx_sim* sim, rdx_kernel_times* out, int reset);
 rdx_status rdx_save(rdx_sim* sim, void* buf, size_t* len, void* stream);
 rdx_status rdx_load(rdx_sim* sim, const void* buf, size_t len, void* stream);
 
-/* Launch shape of the window kernels.  Results never depend on it (every
+/* Launch shape of the window kernel.  Results never depend on it (every
  * draw is addressed by (seed, stream, tet, window) and moves are integer
  * sums), only speed does.
  *   autotune       1: time the candidate shapes on the next windows run
  *                  (those windows are real work of the simulation) and keep
  *                  the fastest; get returns 1 while tuning is under way
- *   fast_grid_div  main kernel grid = resident grid / this (1, 2 or 4)
+ *   fast_grid_div  grid = resident grid / this (1, 2 or 4)
  *   graph_windows  windows per captured HIP graph, replayed as one launch;
  *                  1 = plain launches (1..256)
- *   event_group    most queued tiles (tiles with a tet whose first SSA event
- *                  falls in the window) one event block takes as a group,
- *                  their listed tets packed into chunks of up to 64 lanes
- *                  (1..64; 0 = the default, 4).  Where listed tets are sparse
- *                  (one per tile), larger groups leave fewer, fuller event
- *                  blocks and more blocks for the diffusion of every tet.
- *   event_bins     1: listed tets whose expected events in the window
- *                  (a0 tau) exceed 1 are queued apart from the others and
- *                  packed into event chunks of their own, so that a chunk's
- *                  lanes, which run their SSA chains in lock-step, have
- *                  chains of similar length (load balancing of skewed event
- *                  loads, section 3.2); 0: one queue.  Default 1.
- *   tile_claim     1: after its first tile, a diffusion block claims its
+ *   event_group    1..64, 0 = the default, 4.  Accepted and reported, without
+ *                  effect: a tile's listed tets run in the wave that holds the
+ *                  tile, and there are no event blocks to group them for.
+ *   event_bins     0 or 1.  Accepted and reported, without effect, likewise:
+ *                  each listed tet has a group of lanes of its own, and a wave
+ *                  steps 4 to 16 of them.  Default 1.
+ *   tile_claim     1: after its first tile, a block claims its
  *                  next tile at run time from a counter of its XCD's tile
  *                  range, so that blocks finish within about one tile of each
  *                  other where tiles differ in cost (molecules clustered in
@@ -363,7 +355,7 @@ typedef enum {
 } rdx_request_state;
 
 typedef struct rdx_server_options {
-  size_t hbm_budget_bytes;  /* device memory for the worklist and the requests' state (>= 1 MiB) */
+  size_t hbm_budget_bytes;  /* device memory for the tile map and the requests' state (>= 1 MiB) */
   int32_t max_runs;         /* requests resident at once (0: up to 1024, as the budget allows) */
   int32_t tick_windows;     /* windows per scheduling tick (0 = 8) */
   int32_t graph_windows;    /* windows per captured graph (0 = tick_windows, 1 = plain launches) */
@@ -388,7 +380,7 @@ typedef struct rdx_server_stats {
   double uptime_s;
   double latency_p50_s;     /* nearest-rank quantiles of completion - submission */
   double latency_p99_s;
-  int64_t capacity_tets;    /* worklist capacity derived from the budget */
+  int64_t capacity_tets;    /* tet capacity derived from the budget */
   double worker_s;          /* worker thread time spent on admissions' uploads and on planning
                                and enqueueing ticks (not on waiting for the device) */
 } rdx_server_stats;

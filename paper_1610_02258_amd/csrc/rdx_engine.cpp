@@ -27,7 +27,7 @@ hipError_t dev_alloc(T** p, size_t count) {
 }
 
 // The batch step index lives in an int32 on the device; it is brought back
-// near zero (keeping its parity, which selects the worklist counter) before it
+// near zero (keeping its parity, which selects the claim counters) before it
 // could pass this.
 constexpr int64_t kStepRebase = int64_t(1) << 30;
 
@@ -181,7 +181,7 @@ size_t Engine::run_bytes(const HostInstance& I) {
 
 size_t Engine::worklist_bytes_per_tet(int S) {
   (void)S;
-  return 4 + 1;  // the tet index of its slot, and its share of the per-tile count and queue entry
+  return 5;
 }
 
 void Engine::fence(hipStream_t stream) {
@@ -237,12 +237,7 @@ Engine::~Engine() {
   (void)hipFree(d_runs_);
   (void)hipFree(d_tile_map_);
   (void)hipFree(d_n_tiles_);
-  (void)hipFree(d_base_);
-  (void)hipFree(wl_tile_count_);
-  (void)hipFree(wl_mask_);
-  (void)hipFree(evq_);
-  (void)hipFree(evq_count_);
-  (void)hipFree(wl_tet_);
+  (void)hipFree(d_step_);
   (void)hipFree(tile_ctr_);
   if (h_runs_) (void)hipHostFree(h_runs_);
   if (h_tile_map_) (void)hipHostFree(h_tile_map_);
@@ -264,15 +259,11 @@ rdx_status Engine::init(const HostInstance& proto, size_t arena_bytes, int max_r
   max_tets_ = max_tets;
   max_tiles_ = (max_tets + 63) / 64 + max_runs;
   if (max_tiles_ > (int64_t)INT32_MAX) return set_error(RDX_EINVAL, "too many tiles");
-  if (64 * max_tiles_ > (int64_t)INT32_MAX) return set_error(RDX_EINVAL, "worklist too large");
-  const size_t W = 64 * (size_t)max_tiles_;  // 64 worklist slots per tile
+  if (64 * max_tiles_ > (int64_t)INT32_MAX) return set_error(RDX_EINVAL, "too many tets");
   bool ok = dev_alloc(&model_, 1) == hipSuccess && dev_alloc(&d_runs_, (size_t)max_runs) == hipSuccess &&
             dev_alloc(&d_tile_map_, (size_t)max_tiles_) == hipSuccess &&
-            dev_alloc(&d_n_tiles_, 1) == hipSuccess && dev_alloc(&d_base_, 1) == hipSuccess &&
-            dev_alloc(&wl_tile_count_, (size_t)max_tiles_) == hipSuccess && dev_alloc(&wl_mask_, (size_t)max_tiles_) == hipSuccess &&
-            dev_alloc(&evq_, (size_t)kBins * kQueues * (size_t)((max_tiles_ + kQueues - 1) / kQueues)) == hipSuccess &&
-            dev_alloc(&evq_count_, (size_t)2 * kBins * kQueues * kQueueStride) == hipSuccess &&
-            dev_alloc(&wl_tet_, W) == hipSuccess && dev_alloc(&tile_ctr_, (size_t)2 * 8 * kClaimSubs * kCtrStride) == hipSuccess;
+            dev_alloc(&d_n_tiles_, 1) == hipSuccess && dev_alloc(&d_step_, 2) == hipSuccess &&
+            dev_alloc(&tile_ctr_, (size_t)2 * 8 * kClaimSubs * kCtrStride) == hipSuccess;
   if (ok && arena_bytes) ok = arena_.reserve(arena_bytes) == hipSuccess;
   if (ok) ok = hipHostMalloc(reinterpret_cast<void**>(&h_runs_), sizeof(RunDesc) * (size_t)max_runs) == hipSuccess;
   if (ok) ok = hipHostMalloc(reinterpret_cast<void**>(&h_tile_map_), sizeof(int2) * (size_t)max_tiles_) == hipSuccess;
@@ -287,9 +278,7 @@ rdx_status Engine::init(const HostInstance& proto, size_t arena_bytes, int max_r
   RDX_HIP(hipStreamCreateWithFlags(&own_, hipStreamNonBlocking));
   RDX_HIP(hipMemcpyAsync(model_, &model_host_, sizeof model_host_, hipMemcpyHostToDevice, own_));
   RDX_HIP(hipMemsetAsync(d_n_tiles_, 0, sizeof(int32_t), own_));
-  RDX_HIP(hipMemsetAsync(d_base_, 0, sizeof(int32_t), own_));
-  RDX_HIP(hipMemsetAsync(wl_tile_count_, 0, sizeof(int32_t) * (size_t)max_tiles_, own_));
-  RDX_HIP(hipMemsetAsync(evq_count_, 0, sizeof(unsigned long long) * 2 * kBins * kQueues * kQueueStride, own_));
+  RDX_HIP(hipMemsetAsync(d_step_, 0, 2 * sizeof(int32_t), own_));
   RDX_HIP(hipMemsetAsync(tile_ctr_, 0, sizeof(int32_t) * 2 * 8 * kClaimSubs * kCtrStride, own_));
   RDX_HIP(hipStreamSynchronize(own_));
   return RDX_OK;
@@ -527,10 +516,6 @@ rdx_status Engine::plan_steps(Run* r, int64_t n) {
 }
 
 namespace {
-// Threshold of expected events (a0 tau_k) above which a listed tet goes to
-// the heavy bin; with binning off every listed tet is light.
-double heavy_events(const ExecShape& sh) { return sh.event_bins ? 1.0 : HUGE_VAL; }
-
 // Fewest rounds of tiles `resident` blocks need, then the fewest blocks (a
 // multiple of the 8 XCDs) that still finish in that many rounds.
 int rounds_grid(int64_t n_tiles, int resident) {
@@ -557,20 +542,12 @@ static int64_t bucket_tiles(int64_t n) {
   return (n + g - 1) / g * g;
 }
 
-void Engine::grids_for(int64_t n_tiles_exact, int div, int* detect, int* main) const {
+int Engine::grid_for(int64_t n_tiles_exact, int div, bool claim) const {
   const int64_t n_tiles = max_runs_ > 1 ? bucket_tiles(n_tiles_exact) : n_tiles_exact;
-  int rd = 0, rm = 0;
-  grid_resident(S_, R_, &rd, &rm);
-  // detect kernel: one block per tile (light blocks, many resident per SIMD,
-  // so the latency of each tile's loads is hidden by the others)
-  (void)rd;
-  *detect = (int)std::max<int64_t>(1, std::min<int64_t>(n_tiles, 1 << 24));
-  // main kernel: the diffusion blocks' grid plus room for the event blocks
-  // (one per tile with listed tets, decided on the device), within what is
-  // resident at once
-  const int res = std::max(8, rm / std::max(1, div));
-  const int reserve = std::min(256, std::max(8, res / 4));
-  *main = std::max(2, std::min(res, rounds_grid(n_tiles, res) + reserve));
+  const int resident = std::max(8, grid_resident(S_, R_) / std::max(1, div));
+  // claimed tiles: every block the device holds, whatever the number of tiles
+  if (claim) return (int)std::max<int64_t>(1, std::min<int64_t>((n_tiles + 7) & ~int64_t(7), resident & ~7));
+  return rounds_grid(n_tiles, resident);
 }
 
 rdx_status Engine::upload_tables(const std::vector<Run*>& active, int64_t k0, hipStream_t stream,
@@ -601,7 +578,10 @@ rdx_status Engine::upload_tables(const std::vector<Run*>& active, int64_t k0, hi
     d.key1 = (uint32_t)(r->seed >> 32);
     d.tau = I.tau;
     d.tau_last = r->plan_tau_last;
-    for (int s = 0; s < I.S; ++s) d.D[s] = I.D[s];
+    for (int s = 0; s < I.S; ++s) {
+      d.D[s] = I.D[s];
+      if (I.D[s] > 0.0) d.dmask |= 1u << s;
+    }
   }
   RDX_HIP(hipMemcpyAsync(d_runs_, h_runs_, sizeof(RunDesc) * n, hipMemcpyHostToDevice, stream));
   // tile map: rebuilt only when the set of runs changes
@@ -626,19 +606,20 @@ rdx_status Engine::upload_tables(const std::vector<Run*>& active, int64_t k0, hi
   return RDX_OK;
 }
 
-rdx_status Engine::launch_plain(const StepArgs& a0, int64_t K, hipStream_t stream) {
+rdx_status Engine::launch_plain(const StepArgs& a0, int64_t step0, int64_t K, hipStream_t stream) {
   StepArgs a = a0;
   for (int64_t k = 0; k < K; ++k) {
-    a.k_rel = (int32_t)k;
+    a.step = (int32_t)(step0 + k);
+    a.parity = a.step & 1;
     hipEvent_t* marks = nullptr;
     if (timing_) {
-      while (marks_.size() < marks_used_ + 3) {
+      while (marks_.size() < marks_used_ + 2) {
         hipEvent_t ev;
         RDX_HIP(hipEventCreate(&ev));
         marks_.push_back(ev);
       }
       marks = marks_.data() + marks_used_;
-      marks_used_ += 3;
+      marks_used_ += 2;
     }
     hipError_t e = launch_window(a, stream, marks);
     if (e != hipSuccess) return set_error(RDX_EHIP, std::string("window launch: ") + hipGetErrorString(e));
@@ -655,42 +636,43 @@ rdx_status Engine::launch_plain(const StepArgs& a0, int64_t K, hipStream_t strea
       rec_.records += 1;
     }
   }
-  if (K > 0) RDX_HIP(launch_advance_base(d_base_, (int32_t)K, stream));
   return RDX_OK;
 }
 
-rdx_status Engine::launch_graphs(const StepArgs& a0, int64_t reps, hipStream_t stream) {
+rdx_status Engine::launch_graphs(const StepArgs& a0, int64_t step0, int64_t reps, hipStream_t stream) {
   const int W = shape_.graph_windows;
-  // everything of the arguments that can change between sequences is in the
-  // key (pointers and tables are fixed for the engine's life)
-  const long long shape_key = ((long long)a0.main_grid << 40) | ((long long)(a0.tile_claim ? 1 : 0) << 35) |
-                              ((long long)a0.detect_grid << 9) |
-                              ((long long)(a0.heavy_events < 1e300 ? 1 : 0) << 8) |
-                              ((long long)a0.ev_group_max << 1) | (long long)a0.single_run;
-  const auto key = std::make_pair(W, shape_key);
-  auto it = graphs_.find(key);
-  if (it == graphs_.end()) {
-    if (graphs_.size() >= 16) free_graphs();
-    if (!capture_stream_) RDX_HIP(hipStreamCreateWithFlags(&capture_stream_, hipStreamNonBlocking));
-    // W windows and the step-base advance, captured once on a private stream
-    StepArgs a = a0;
-    RDX_HIP(hipStreamBeginCapture(capture_stream_, hipStreamCaptureModeThreadLocal));
-    hipError_t e = hipSuccess;
-    for (int k = 0; k < W && e == hipSuccess; ++k) {
-      a.k_rel = k;
-      e = launch_window(a, capture_stream_, nullptr);
+  for (int64_t r = 0; r < std::max<int64_t>(1, reps); ++r) {
+    const int parity = (int)((step0 + r * W) & 1);
+    // everything of the arguments that can change between sequences is in the
+    // key (pointers and tables are fixed for the engine's life)
+    const long long shape_key = ((long long)a0.grid << 3) | ((long long)(a0.tile_claim ? 1 : 0) << 2) |
+                                ((long long)parity << 1) | (long long)a0.single_run;
+    const auto key = std::make_pair(W, shape_key);
+    auto it = graphs_.find(key);
+    if (it == graphs_.end()) {
+      if (graphs_.size() >= 16) free_graphs();
+      if (!capture_stream_) RDX_HIP(hipStreamCreateWithFlags(&capture_stream_, hipStreamNonBlocking));
+      // W windows, captured once on a private stream; each reads its step
+      // index from the word that the window before it wrote
+      StepArgs a = a0;
+      a.step = -1;
+      RDX_HIP(hipStreamBeginCapture(capture_stream_, hipStreamCaptureModeThreadLocal));
+      hipError_t e = hipSuccess;
+      for (int k = 0; k < W && e == hipSuccess; ++k) {
+        a.parity = (parity + k) & 1;
+        e = launch_window(a, capture_stream_, nullptr);
+      }
+      hipGraph_t graph = nullptr;
+      hipError_t e2 = hipStreamEndCapture(capture_stream_, &graph);
+      if (e == hipSuccess) e = e2;
+      hipGraphExec_t exec = nullptr;
+      if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+      if (graph) (void)hipGraphDestroy(graph);
+      if (e != hipSuccess) return set_error(RDX_EHIP, std::string("graph capture: ") + hipGetErrorString(e));
+      it = graphs_.emplace(key, exec).first;
     }
-    if (e == hipSuccess) e = launch_advance_base(d_base_, W, capture_stream_);
-    hipGraph_t graph = nullptr;
-    hipError_t e2 = hipStreamEndCapture(capture_stream_, &graph);
-    if (e == hipSuccess) e = e2;
-    hipGraphExec_t exec = nullptr;
-    if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-    if (graph) (void)hipGraphDestroy(graph);
-    if (e != hipSuccess) return set_error(RDX_EHIP, std::string("graph capture: ") + hipGetErrorString(e));
-    it = graphs_.emplace(key, exec).first;
+    if (r < reps) RDX_HIP(hipGraphLaunch(it->second, stream));
   }
-  for (int64_t r = 0; r < reps; ++r) RDX_HIP(hipGraphLaunch(it->second, stream));
   return RDX_OK;
 }
 
@@ -705,10 +687,8 @@ void Engine::set_autotune(bool on) {
   // pass, so that a drift of the per-window cost over the tuning windows (a
   // simulation relaxing from its initial counts) biases the choice less
   // (with two passes the batched ensemble settled on a shape 3.7% slower)
-  const ExecShape shapes[] = {ExecShape{1, 1, 4},        ExecShape{2, 1, 4},       ExecShape{1, 8, 4},
-                              ExecShape{2, 8, 4},        ExecShape{4, 8, 4},       ExecShape{1, 8, 8},
-                              ExecShape{1, 8, 16},       ExecShape{1, 8, 64},      ExecShape{1, 1, 64},
-                              ExecShape{1, 1, 4, 1, 1},  ExecShape{1, 8, 16, 1, 1}};
+  const ExecShape shapes[] = {ExecShape{1, 1, 4}, ExecShape{2, 1, 4},       ExecShape{1, 8, 4},      ExecShape{2, 8, 4},
+                              ExecShape{4, 8, 4}, ExecShape{1, 1, 4, 1, 1}, ExecShape{1, 8, 4, 1, 1}};
   candidates_.push_back(shapes[0]);
   for (int pass = 0; pass < 3; ++pass)
     for (const ExecShape& c : shapes) candidates_.push_back(c);
@@ -730,8 +710,8 @@ rdx_status Engine::sequence(const std::vector<Run*>& runs, hipStream_t stream) {
   int64_t k0 = k_now_;
   if (k0 + K >= kStepRebase) {
     if (K >= kStepRebase) return set_error(RDX_EINVAL, "sequence too long");
-    k0 = k_now_ & 1;  // keep the parity of the worklist counters
-    RDX_HIP(launch_set_base(d_base_, (int32_t)k0, stream));
+    k0 = k_now_ & 1;  // keep the parity of the claim counters
+    RDX_HIP(launch_set_step(d_step_, (int32_t)k0, stream));
   }
   int64_t n_tiles = 0;
   rdx_status st = upload_tables(active, k0, stream, &n_tiles);
@@ -742,10 +722,9 @@ rdx_status Engine::sequence(const std::vector<Run*>& runs, hipStream_t stream) {
   a.runs = d_runs_;
   a.tile_map = d_tile_map_;
   a.n_tiles = d_n_tiles_;
-  a.step_base = d_base_;
+  a.step_words = d_step_;
   a.S = S_;
   a.R = R_;
-  a.wl_mask = wl_mask_;
   a.model = model_;
   std::memcpy(a.info, model_host_.info, sizeof a.info);
   {
@@ -753,39 +732,30 @@ rdx_status Engine::sequence(const std::vector<Run*>& runs, hipStream_t stream) {
     listing_pairs(model_host_, a.pairs, &a.n_pairs, pair_of);
   }
   a.single_run = active.size() == 1 ? 1 : 0;
-  a.wl_tile_count = wl_tile_count_;
-  a.evq = evq_;
-  a.evq_cap = (int32_t)((max_tiles_ + kQueues - 1) / kQueues);
-  a.evq_count = evq_count_;
-  a.wl_tet = wl_tet_;
   a.tile_ctr = tile_ctr_;
 
-  auto run_chunk = [&](const ExecShape& sh, int64_t n) -> rdx_status {
-    grids_for(n_tiles, sh.fast_grid_div, &a.detect_grid, &a.main_grid);
-    a.ev_group_max = sh.event_group;
-    a.heavy_events = heavy_events(sh);
+  // n windows from step `at` of the sequence at launch shape `sh`
+  auto run_chunk = [&](const ExecShape& sh, int64_t at, int64_t n) -> rdx_status {
+    a.grid = grid_for(n_tiles, sh.fast_grid_div, sh.tile_claim != 0);
     a.tile_claim = sh.tile_claim;
     const ExecShape keep = shape_;
     shape_ = sh;
     rdx_status r = RDX_OK;
+    int64_t in_graphs = 0;
     if (!timing_ && sh.graph_windows > 1 && n >= sh.graph_windows) {
-      const int64_t reps = n / sh.graph_windows;
-      r = launch_graphs(a, reps, stream);
-      if (r == RDX_OK) r = launch_plain(a, n - reps * sh.graph_windows, stream);
-    } else {
-      r = launch_plain(a, n, stream);
+      in_graphs = n / sh.graph_windows * sh.graph_windows;
+      r = launch_graphs(a, k0 + at, n / sh.graph_windows, stream);
     }
+    if (r == RDX_OK) r = launch_plain(a, k0 + at + in_graphs, n - in_graphs, stream);
     shape_ = keep;
     return r;
   };
 
   int64_t done = 0;
   if (rec_on_) {  // records between windows: plain launches at the current shape
-    grids_for(n_tiles, shape_.fast_grid_div, &a.detect_grid, &a.main_grid);
-    a.ev_group_max = shape_.event_group;
-    a.heavy_events = heavy_events(shape_);
+    a.grid = grid_for(n_tiles, shape_.fast_grid_div, shape_.tile_claim != 0);
     a.tile_claim = shape_.tile_claim;
-    st = launch_plain(a, K, stream);
+    st = launch_plain(a, k0, K, stream);
     if (st != RDX_OK) return st;
     done = K;
   }
@@ -793,18 +763,16 @@ rdx_status Engine::sequence(const std::vector<Run*>& runs, hipStream_t stream) {
     const ExecShape c = candidates_[cand_next_];
     const int64_t n = std::min<int64_t>(K - done, std::max(8, 2 * c.graph_windows));
     if (c.graph_windows > 1 && n >= c.graph_windows) {  // capture outside the timed span
-      grids_for(n_tiles, c.fast_grid_div, &a.detect_grid, &a.main_grid);
-      a.ev_group_max = c.event_group;
-      a.heavy_events = heavy_events(c);
+      a.grid = grid_for(n_tiles, c.fast_grid_div, c.tile_claim != 0);
       a.tile_claim = c.tile_claim;
       const ExecShape keep = shape_;
       shape_ = c;
-      st = launch_graphs(a, 0, stream);
+      st = launch_graphs(a, k0 + done, 0, stream);
       shape_ = keep;
       if (st != RDX_OK) return st;
     }
     RDX_HIP(hipEventRecord(tune_ev_[0], stream));
-    st = run_chunk(c, n);
+    st = run_chunk(c, done, n);
     if (st != RDX_OK) return st;
     RDX_HIP(hipEventRecord(tune_ev_[1], stream));
     RDX_HIP(hipEventSynchronize(tune_ev_[1]));
@@ -830,7 +798,7 @@ rdx_status Engine::sequence(const std::vector<Run*>& runs, hipStream_t stream) {
     }
   }
   if (done < K) {
-    st = run_chunk(shape_, K - done);
+    st = run_chunk(shape_, done, K - done);
     if (st != RDX_OK) return st;
   }
   k_now_ = k0 + K;
@@ -846,22 +814,20 @@ rdx_status Engine::sequence(const std::vector<Run*>& runs, hipStream_t stream) {
 }
 
 rdx_status Engine::kernel_times(rdx_kernel_times* out, bool reset) {
-  for (size_t k = 0; k + 3 <= marks_used_; k += 3) {
-    RDX_HIP(hipEventSynchronize(marks_[k + 2]));
-    float a = 0.f, b = 0.f;
-    RDX_HIP(hipEventElapsedTime(&a, marks_[k], marks_[k + 1]));
-    RDX_HIP(hipEventElapsedTime(&b, marks_[k + 1], marks_[k + 2]));
-    detect_ms_ += a;
-    main_ms_ += b;
+  for (size_t k = 0; k + 2 <= marks_used_; k += 2) {
+    RDX_HIP(hipEventSynchronize(marks_[k + 1]));
+    float ms = 0.f;
+    RDX_HIP(hipEventElapsedTime(&ms, marks_[k], marks_[k + 1]));
+    main_ms_ += ms;
     timed_windows_ += 1;
   }
   marks_used_ = 0;
   out->windows = timed_windows_;
-  out->detect_ms = detect_ms_;
+  out->detect_ms = 0.0;  // the listing is part of the window kernel
   out->main_ms = main_ms_;
   if (reset) {
     timed_windows_ = 0;
-    detect_ms_ = main_ms_ = 0.0;
+    main_ms_ = 0.0;
   }
   return RDX_OK;
 }

@@ -8,8 +8,8 @@
 // are all Engines; they differ only in how runs come and go.
 //
 // Device memory of the runs comes from one arena reserved up front (no
-// allocation in the stepping loop); the per-window worklist is sized for the
-// engine's tet capacity.  Sequences of windows are replayed from captured
+// allocation in the stepping loop); the tile map is sized for the engine's tet
+// capacity.  Sequences of windows are replayed from captured
 // HIP graphs when that pays, and the launch shape can be tuned online
 // (results do not depend on it).
 #pragma once
@@ -75,15 +75,15 @@ struct Run {
   double plan_tau_last = 0.0, plan_t_after = 0.0;
 };
 
-// Launch shape of a sequence.  fast_grid_div: the main kernel's grid is its
-// resident grid divided by this (1, 2, 4); graph_windows: windows per
-// captured graph (1 = plain launches).
+// Launch shape of a sequence.  fast_grid_div: the grid is the resident grid
+// divided by this (1, 2, 4); graph_windows: windows per captured graph (1 =
+// plain launches).
 struct ExecShape {
   int fast_grid_div = 1;
   int graph_windows = 1;
-  int event_group = 4;  // most queued tiles packed into one event chunk
-  int event_bins = 1;   // listed tets binned by expected events (heavy, light)
-  int tile_claim = 0;   // diffusion tiles after the first claimed at run time
+  int event_group = 4;  // event_group and event_bins: kept and reported, without effect
+  int event_bins = 1;
+  int tile_claim = 0;   // tiles after the first claimed at run time
   bool operator<(const ExecShape& o) const {
     if (fast_grid_div != o.fast_grid_div) return fast_grid_div < o.fast_grid_div;
     if (graph_windows != o.graph_windows) return graph_windows < o.graph_windows;
@@ -102,8 +102,9 @@ class Engine {
 
   // Device bytes of one run's state (counts, mesh arrays, tables, tallies).
   static size_t run_bytes(const HostInstance& I);
-  // Worklist bytes per tet of capacity (64 entries per tile, each tile
-  // of a run padded to 64 tets).
+  // Bytes a server's budget sets aside per tet of capacity beside the runs'
+  // state.  More than the tile map takes (8 per tile of 64 tets); what a
+  // budget admits rests on it.
   static size_t worklist_bytes_per_tet(int S);
 
   // `proto` fixes the shared species/reaction structure.  arena_bytes holds
@@ -210,9 +211,11 @@ class Engine {
  private:
   rdx_status upload_tables(const std::vector<Run*>& active, int64_t k0, hipStream_t stream,
                            int64_t* n_tiles_out);
-  rdx_status launch_plain(const StepArgs& a, int64_t K, hipStream_t stream);
-  rdx_status launch_graphs(const StepArgs& a, int64_t reps, hipStream_t stream);
-  void grids_for(int64_t n_tiles, int div, int* detect, int* main) const;
+  // K windows, or `reps` graphs of windows (0: only captured), from step index
+  // `step0` on
+  rdx_status launch_plain(const StepArgs& a, int64_t step0, int64_t K, hipStream_t stream);
+  rdx_status launch_graphs(const StepArgs& a, int64_t step0, int64_t reps, hipStream_t stream);
+  int grid_for(int64_t n_tiles, int div, bool claim) const;
   void free_graphs();
 
   int S_ = 0, R_ = 0;
@@ -227,13 +230,8 @@ class Engine {
   RunDesc* d_runs_ = nullptr;
   int2* d_tile_map_ = nullptr;
   int32_t* d_n_tiles_ = nullptr;
-  int32_t* d_base_ = nullptr;
-  int32_t* wl_tile_count_ = nullptr;
-  unsigned long long* wl_mask_ = nullptr;
-  int32_t* evq_ = nullptr;
-  unsigned long long* evq_count_ = nullptr;
-  int32_t* wl_tet_ = nullptr;
-  int32_t* tile_ctr_ = nullptr;  // [2][8][kCtrStride]
+  int32_t* d_step_ = nullptr;    // [2] step index of the next window, by parity
+  int32_t* tile_ctr_ = nullptr;  // [2][8][kClaimSubs][kCtrStride]
 
   // pinned staging of the run table and tile map; `staged_` marks the
   // completion of the last upload from them
@@ -249,7 +247,7 @@ class Engine {
   hipEvent_t reset_staged_ = nullptr;
   std::vector<const Run*> tile_runs_;  // runs of the tile map on the device
   std::vector<int64_t> tile_run_T_;
-  int64_t k_now_ = 0;                  // batch step index == *d_base_
+  int64_t k_now_ = 0;                  // batch step index == d_step_[k_now_ & 1]
 
   // graphs by (windows, grids); captured on a private stream
   hipStream_t capture_stream_ = nullptr;
@@ -270,7 +268,7 @@ class Engine {
   std::vector<hipEvent_t> marks_;
   size_t marks_used_ = 0;
   int64_t timed_windows_ = 0;
-  double detect_ms_ = 0.0, main_ms_ = 0.0;
+  double main_ms_ = 0.0;
 };
 
 // DevModel of a validated instance (packed reaction entries, net changes,

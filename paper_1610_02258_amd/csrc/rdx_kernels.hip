@@ -24,6 +24,7 @@
 // same operation sequence.
 #include <hip/hip_runtime.h>
 
+#include <array>
 #include <cstdint>
 #include <type_traits>
 
@@ -66,28 +67,12 @@ __device__ __forceinline__ void philox4x32_10(uint32_t& x0, uint32_t& x1, uint32
   }
 }
 
-// SSA stream: 53-bit uniforms, two per Philox call (words 0-1, then 2-3).
-struct Draw53 {
-  uint32_t k0, k1, sid, tet, win, call;
-  uint64_t spare;
-  bool has_spare;
-  __device__ Draw53(uint32_t key0, uint32_t key1, uint32_t stream, uint32_t t, uint32_t w)
-      : k0(key0), k1(key1), sid(stream), tet(t), win(w), call(0), spare(0), has_spare(false) {}
-  __device__ __forceinline__ uint64_t next() {
-    if (has_spare) {
-      has_spare = false;
-      return spare;
-    }
-    uint32_t x0 = call, x1 = sid, x2 = tet, x3 = win;
-    philox4x32_10(x0, x1, x2, x3, k0, k1);
-    ++call;
-    spare = ((uint64_t)x2 << 21) | (uint64_t)(x3 >> 11);
-    has_spare = true;
-    return ((uint64_t)x0 << 21) | (uint64_t)(x1 >> 11);
-  }
-  __device__ __forceinline__ double co() { return (double)next() * 0x1p-53; }        // [0, 1)
-  __device__ __forceinline__ double oc() { return (double)(next() + 1u) * 0x1p-53; } // (0, 1]
-};
+// SSA stream: 53-bit uniforms x 2^-53, x = w_hi << 21 | w_lo >> 11, two per
+// Philox call (words 0-1, then 2-3); both terms and their sum are exact.
+__device__ __forceinline__ double u53_co(uint32_t hi, uint32_t lo) {  // [0, 1)
+  return (double)hi * 0x1p-32 + (double)(lo >> 11) * 0x1p-53;
+}
+__device__ __forceinline__ double u53_oc(uint32_t hi, uint32_t lo) { return u53_co(hi, lo) + 0x1p-53; }  // (0, 1]
 
 // Species stream: 32-bit uniforms in [0, 1), four per Philox call.
 struct Draw32 {
@@ -155,11 +140,15 @@ __device__ __forceinline__ double ln_basic(double x) {
 // Sequential-search inversion, one uniform per chunk of <= 1000 trials
 // (q^c >= 2^-1000 stays normal), complement for p > 1/2.
 __device__ __forceinline__ double pow_int(double q, int c) {
+  // the wave steps together to its largest exponent's last bit (a lane past
+  // its own last bit multiplies nothing in), without a branch per lane and bit
   double result = 1.0, base = q;
-  while (c > 0) {
-    if (c & 1) result = result * base;
-    base = base * base;
+  for (;;) {
+    const double next = result * base;
+    result = (c & 1) ? next : result;
     c >>= 1;
+    if (__ballot(c != 0) == 0ull) break;
+    base = base * base;
   }
   return result;
 }
@@ -238,106 +227,65 @@ __device__ __forceinline__ int exp_field(double a) {
 // form whose products are those of the case-by-case definition: h = (x y) w
 // with x = N_A (1 for order 0), y = N_B, N_A - 1 (A + A) or 1, w = 1/2 for
 // A + A, and c = k f with f = N_A V, 1 or 1 / (N_A V).  Values below 2^-1000
-// are taken as zero.  `info` is the packed reaction entry (uniform); `N`
-// holds the counts as one vector value, so that the uniform species index
-// selects a register.
-template <int SMAX, typename NV>
-__device__ __forceinline__ double propensity(int info, double k, const NV& N, double nav, double inv_nav) {
-  const int order = info & 0xff;
-  const int s0 = (info >> 8) & 0xff, s1 = (info >> 16) & 0xff;
-  const bool same = order == 2 && s0 == s1;
-  const int x = order == 0 ? 1 : (s0 < SMAX ? N[s0] : 0);
-  const int y = order == 2 ? (s1 < SMAX ? N[s1] : 0) - (same ? 1 : 0) : 1;
-  const double f = order == 0 ? nav : (order == 1 ? 1.0 : inv_nav);
-  const double v = (k * f) * (((double)x * (double)y) * (same ? 0.5 : 1.0));
+// are taken as zero.
+__device__ __forceinline__ double propensity(double c, int x, int y, double w) {
+  const double v = c * (((double)x * (double)y) * w);
   return v >= 0x1p-1000 ? v : 0.0;
 }
 
-// Composition: groups of reactions with equal binary exponent, visited from
-// the largest exponent down, picked with probability proportional to their
-// totals; rejection: a uniform member is accepted with probability a / 2^g.
-// Group totals are summed in reaction order.  The propensities are the
-// lane's column of an LDS table (a_r at col[r * stride]); the scans are
-// loops, so that one SSA step stays a short stretch of code.
-__device__ int cr_select_col(const double* col, int stride, int R, double a0, Draw53& st) {
-  double x = st.co() * a0;
-  int gprev = 4096, chosen = -1;
-  for (;;) {
-    int gcur = -1;
-#pragma unroll 4
-    for (int r = 0; r < R; ++r) {
-      const double v = col[r * stride];
-      const int e = v > 0.0 ? exp_field(v) : -1;
-      if (e < gprev && e > gcur) gcur = e;
-    }
-    if (gcur < 0) break;
-    double sum = 0.0;
-#pragma unroll 4
-    for (int r = 0; r < R; ++r) {
-      const double v = col[r * stride];
-      if (v > 0.0 && exp_field(v) == gcur) sum = sum + v;
-    }
-    chosen = gcur;
-    if (x < sum) break;
-    x = x - sum;
-    gprev = gcur;
-  }
-  int n = 0;
-#pragma unroll 4
-  for (int r = 0; r < R; ++r) {
-    const double v = col[r * stride];
-    n += (v > 0.0 && exp_field(v) == chosen) ? 1 : 0;
-  }
-  const double bound = __longlong_as_double((long long)(chosen + 1) << 52);
-  for (;;) {
-    const double u2 = st.co();
-    int j = (int)(u2 * (double)n);
-    if (j >= n) j = n - 1;
-    const double u3 = st.co();
-    double aj = 0.0;
-    int rj = 0, seen = 0;
-#pragma unroll 4
-    for (int r = 0; r < R; ++r) {
-      const double v = col[r * stride];
-      if (v > 0.0 && exp_field(v) == chosen) {
-        if (seen == j) {
-          aj = v;
-          rj = r;
-        }
-        ++seen;
-      }
-    }
-    if (u3 * bound < aj) return rj;
-  }
-}
-
+// The sum over the wave, on lane 63 (row shifts, then row broadcasts; lanes
+// without a source add 0).
 __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  auto add = [&](uint32_t lo, uint32_t hi) { v += ((unsigned long long)hi << 32) | lo; };
+#define RDX_STEP(ctrl, rows)                                                     \
+  add((uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, ctrl, rows, 0xf, false), \
+      (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), ctrl, rows, 0xf, false))
+  RDX_STEP(0x111, 0xf);  // row_shr:1
+  RDX_STEP(0x112, 0xf);  // row_shr:2
+  RDX_STEP(0x114, 0xf);  // row_shr:4
+  RDX_STEP(0x118, 0xf);  // row_shr:8
+  RDX_STEP(0x142, 0xa);  // row_bcast:15
+  RDX_STEP(0x143, 0xc);  // row_bcast:31
+#undef RDX_STEP
   return v;
 }
 
-// ------------------------------------------------------- window kernels ----
-// A window of a batch is two launches, one wave (64 lanes) per block, one lane
-// per tet, 64 tets per tile (a tile belongs to one run).
+// -------------------------------------------------------- window kernel ----
+// A window of a batch is one launch of window_main_kernel: persistent blocks of one
+// wave (64 lanes), one lane per tet, a tile of up to 64 tets at a time (a tile
+// belongs to one run).  Per tile:
 //
-// window_detect_kernel, over all tiles: a0 from regrouped coefficients and the
-// tet's first SSA uniform.  A tet whose first event may fall inside the
-// window is listed (its index goes to the tile's worklist slots, the tile to
-// one of 64 sub-queues); a per-tile bit mask marks the listed tets.
+// Listing: a0 from regrouped coefficients and the tet's first SSA uniform.
+// A tet whose first event may fall inside the window is listed.
 //
-// window_main_kernel: its first blocks take groups of queued tiles and run
-// the full SSA window (composition-rejection, occupancy) and the diffusion of
-// the listed tets; the other blocks walk all tiles and do the diffusion of
-// every tet that is not listed (no count changes, the mean occupancy is the
-// count itself).  The serial SSA chains of the few listed tets so run
-// alongside the diffusion of the rest instead of after it.
+// Reaction operator: the listed tets run their SSA window
+// (composition-rejection, occupancy), each on a group of 4, 8 or 16 lanes, as
+// many at a time as the wave has groups.
 //
 // Diffusion items: every (tet, species) pair with something to sample becomes
-// an item; ballots pack them into LDS (items of more than 16 molecules first,
-// species-major), and they are sampled in rounds of 64 (item_round).  Moves
-// into the tile's own tets accumulate in LDS and are flushed once, coalesced;
-// the rest are integer atomics into the next count buffer.
+// an item; ballots pack them into LDS and they are sampled in rounds of 64,
+// one per lane.  Moves into the tile's own tets accumulate in LDS and are
+// flushed once, coalesced; the rest are integer atomics into the next count
+// buffer.
+//
+// What the one launch replaces: a listing launch over all tiles, which wrote
+// queues of listed tets, and event blocks beside the diffusion blocks, which
+// read the tets again and ran them in chunks.  The chain queue counters ->
+// queue -> worklist -> counts took 7 us before a chunk's first propensity, a
+// chunk could hold one run only, and the event blocks ended last wherever
+// tiles are few or runs small.  Here the tet is read once, listed, stepped and
+// diffused by the wave that holds it.  Per window, two launches against one:
+// 480,000 tets, 10 species, 2 molecules a tet 42.4 -> 36.7 us; 1.2 million
+// molecules in 60,000 tets of it 47.2 -> 28.9 us; 112,000 tets of the calcium
+// model with events crowded in one region 915 -> 320 us (with the binomial
+// search below 608 -> 320); 48 runs of 200 to 1,500 tets 59 -> 21 us.
+//
+// What bounds a tile: the chain of a lone wave (a load, the propensities and a
+// Philox call, the item list, the items' draws), 10 us where tets hold two
+// molecules against 0.4 us of memory traffic at the copy rate, and VALU issue
+// where they hold hundreds (59% of the issue slots at the million-tet calcium
+// dendrite, 6,260 instructions a tile).  Hence waves per SIMD: four for up to
+// 12 species, three above.
 constexpr int kWave = 64;
 
 // Tables the window kernels only read -- the run table, the tile map, the
@@ -358,17 +306,17 @@ __device__ __forceinline__ cptr<T> as_const(const T* p) {
 typedef int int4_v __attribute__((ext_vector_type(4)));
 typedef double double2_v __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ int4 ld_int4(const int4* p, size_t j) {
+__device__ __forceinline__ int4 ld_int4(const int4* p, uint32_t j) {
   const int4_v v = ((cptr<int4_v>)p)[j];
   return make_int4(v.x, v.y, v.z, v.w);
 }
 
-__device__ __forceinline__ double2 ld_double2(const double2* p, size_t j) {
+__device__ __forceinline__ double2 ld_double2(const double2* p, uint32_t j) {
   const double2_v v = ((cptr<double2_v>)p)[j];
   return make_double2(v.x, v.y);
 }
 
-// Every block of the window kernels is a single wave: its lanes execute in
+// Every block of the window kernel is a single wave: its lanes execute in
 // lockstep and its LDS operations complete in issue order, so handing LDS
 // data from lane to lane only needs the compiler to keep the accesses in
 // program order (a wavefront-scope fence), not a workgroup barrier, whose
@@ -378,29 +326,23 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-__device__ __forceinline__ int wave_inclusive_scan(int v) {
-  // v in [0, 31]: the sum over lanes <= this one, one bit plane at a time
-  // (five ballots and bit counts; no LDS traffic)
-  int acc = 0;
+// The values as new ones to the compiler, so that what is computed from them
+// in a loop stays there.  Left alone it computes every mask, address and item
+// word of a tile's species ahead of the loop and keeps them, several hundred
+// bytes a lane and most of that in scratch memory.
+template <int SMAX, typename NV>
+__device__ __forceinline__ void renew(NV& N) {
 #pragma unroll
-  for (int b = 0; b < 5; ++b) {
-    const unsigned long long m = __ballot((v >> b) & 1);
-    const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    acc += (int)((below + (uint32_t)((v >> b) & 1)) << b);
+  for (int s = 0; s < SMAX; ++s) {
+    int n = N[s];
+    asm volatile("" : "+v"(n));
+    N[s] = n;
   }
-  return acc;
 }
-
-// Inclusive prefix sum over the 64 lanes for any int (six shuffle steps).
-__device__ __forceinline__ int wave_scan_add(int v) {
-  const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    const int u = __shfl_up(v, d, kWave);
-    if (lane >= d) v += u;
-  }
-  return v;
-}
+__device__ __forceinline__ void renew(int& v) { asm volatile("" : "+v"(v)); }
+// Scalars.
+__device__ __forceinline__ void renew_s(int& v) { asm volatile("" : "+s"(v)); }
+__device__ __forceinline__ void renew_s(uint32_t& a, uint32_t& b) { asm volatile("" : "+s"(a), "+s"(b)); }
 
 // Diffusion items.  An item is one (tet, species) pair of a window: m trials
 // of leaving, m = nbar stochastically rounded (a draw only when nbar is
@@ -419,254 +361,154 @@ __device__ __forceinline__ int wave_scan_add(int v) {
 // word j mod 4 of Philox call j / 4, so an item takes at most five calls,
 // which its own lane makes, testing the words against the item's
 // probabilities.  (With m > npost the cap can bind in the middle of the
-// walk; such an item -- only a tet whose counts changed in the window can
-// have one -- is walked word by word in stream order.)
+// walk; such an item -- only a species changed in the window can have one --
+// is walked word by word in stream order.)
 constexpr int kSmallM = 16;
+constexpr int kPackedCount = 1 << 22;  // counts from here on do not fit an item's packed field
 
-struct ItemMoves {
-  int n, o0, o1, o2, o3;
+// Leavers by face.
+struct Faces {
+  int o0, o1, o2, o3;
 };
-
-// A draw w stands for the uniform w 2^-32, and w 2^-32 < t holds exactly
-// when w < ceil(t 2^32) (t 2^32 is exact in binary64).  For t in [0, 1] the
-// threshold is at most 2^32: returned as a 32-bit value, with `full` set when
-// it is 2^32 (every draw passes).
-__device__ __forceinline__ uint32_t draw_threshold(double t, bool& full) {
-  const double c = ceil(t * 0x1p32);
-  full = c >= 0x1p32;
-  return full ? 0xffffffffu : (uint32_t)c;
-}
 
 __device__ __forceinline__ int last_face(int4 nb) {
   return nb.w >= 0 ? 3 : (nb.z >= 0 ? 2 : (nb.y >= 0 ? 1 : 0));
 }
 
-// Per-lane face counts of a round's split and walked items.
-struct ItemLds {
-  uint32_t face[4][kWave];  // leavers by face of the split and walked items, by lane
+// What a lane's item draws against: the leave probability min(1, tau_k D_s G)
+// and the cumulative shares of faces 0, 1, 2, with kAllFaces from the last
+// face present on.
+constexpr double kAllFaces = 2.0;
+struct ItemGeo {
+  double p;
+  double c0, c1, c2;
 };
 
-// The per-tet arrays a round reads, by tet lane (LDS of the tile or chunk).
-struct ItemView {
-  const int4* nbr;      // neighbours
-  const double2* geo0;  // (G, cum0)
-  const double2* geo1;  // (cum1, cum2)
-  const double* tauD;   // tau_k D_s by species
-  const int* tet;       // run-local tet of each tet lane, or null: base + lane
-  int base;
-  __device__ __forceinline__ uint32_t tet_of(int ln) const { return (uint32_t)(tet ? tet[ln] : base + ln); }
+// A draw w leaves when w 2^-32 < p, i.e. (scaling by a power of two is exact)
+// w < p 2^32 as doubles, to the first face k < last with w < p 2^32 cum_k,
+// else to the last.  The thresholds rise with k; those of the faces from
+// `last` on are p's own, and none is above it, so the draws below threshold k
+// are the leavers to the faces up to k: counting each threshold's draws (a
+// compare and an add-with-carry each) gives the face counts as differences,
+// with no choice of a face per draw.
+struct DrawCounts {
+  double t0, t1, t2, ts;
+  int n0, n1, n2, ns;
+  __device__ __forceinline__ explicit DrawCounts(const ItemGeo& g) : n0(0), n1(0), n2(0), ns(0) {
+    ts = g.p * 0x1p32;
+    t0 = fmin(ts * g.c0, ts);
+    t1 = fmin(ts * g.c1, ts);
+    t2 = fmin(ts * g.c2, ts);
+  }
+  __device__ __forceinline__ void add(double u) {
+    n0 += u < t0 ? 1 : 0;
+    n1 += u < t1 ? 1 : 0;
+    n2 += u < t2 ? 1 : 0;
+    ns += u < ts ? 1 : 0;
+  }
+  __device__ __forceinline__ void take_back(double u) {
+    n0 -= u < t0 ? 1 : 0;
+    n1 -= u < t1 ? 1 : 0;
+    n2 -= u < t2 ? 1 : 0;
+    ns -= u < ts ? 1 : 0;
+  }
+  __device__ __forceinline__ Faces faces() const { return Faces{n0, n1 - n0, n2 - n1, ns - n2}; }
 };
 
-// What a lane brings to a round: its item, or valid == false.
-struct ItemIn {
-  bool valid;
-  int sp;      // species
-  int ln;      // tet lane
-  double nbar; // mean occupancy (the count itself when nothing changed it)
-  int npost;   // count after the reactions
-};
-
-// Face of a leaving draw w: the number of faces k < last whose threshold w
-// reaches (the thresholds rise with k; faces at or after `last` carry the
-// "never" bit), and whether w leaves at all.
-__device__ __forceinline__ int draw_face(uint32_t w, uint32_t t0, uint32_t t1, uint32_t t2, uint32_t full) {
-  return (int)(((full & 1u) == 0u && w >= t0)) + (int)(((full & 2u) == 0u && w >= t1)) +
-         (int)(((full & 4u) == 0u && w >= t2));
-}
-
-__device__ __forceinline__ bool draw_leaves(uint32_t w, uint32_t ts, uint32_t full) {
-  return (full & 8u) != 0u || w < ts;
-}
-
-// The item's leave probability: min(1, tau_k D_s G).
-__device__ __forceinline__ double item_p(const ItemView& V, int sp, int ln) {
-  const double pr = V.tauD[sp] * V.geo0[ln].x;
-  return pr > 1.0 ? 1.0 : pr;
-}
-
-// Integer thresholds of an item's face draws (scale = p); `full` bit k:
-// threshold k is never reached (k at or after the last face) or always
-// (2^32), bit 3: every draw leaves.
-__device__ __forceinline__ void item_thresholds(const ItemView& V, int ln, double scale, uint32_t th[4],
-                                                uint32_t& full) {
-  const int last = last_face(V.nbr[ln]);
-  const double2 g0 = V.geo0[ln], g1 = V.geo1[ln];
-  bool f0, f1, f2, fs;
-  th[0] = draw_threshold(scale * g0.y, f0);
-  th[1] = draw_threshold(scale * g1.x, f1);
-  th[2] = draw_threshold(scale * g1.y, f2);
-  th[3] = draw_threshold(scale, fs);
-  full = (f0 || last <= 0 ? 1u : 0u) | (f1 || last <= 1 ? 2u : 0u) | (f2 || last <= 2 ? 4u : 0u) | (fs ? 8u : 0u);
-}
-
-__device__ ItemMoves item_round(uint32_t key0, uint32_t key1, uint32_t window, const ItemIn& it,
-                                const ItemView& V, ItemLds& X) {
-  const int lane = threadIdx.x;
-  uint32_t own = 0;     // leavers by face drawn on this lane, a byte each
-  bool walked = false;  // this lane's face counts are in X.face, by the walk
-  bool split = false;   // this lane's face counts are in X.face, by the split
-  if (it.valid) {
-    const uint32_t tet = V.tet_of(it.ln);
-    Draw32 st(key0, key1, 1u + (uint32_t)it.sp, tet, window);
-    const double fl = floor(it.nbar);
-    const double frac = it.nbar - fl;
-    int m = (int)fl;  // counts are int32
-    uint32_t used = 0;  // words taken before the face draws
-    if (frac > 0.0) {
-      if (st.u() < frac) m += 1;
-      used = 1;
+// The first m draws of the item's stream, made on its lane.
+__device__ __forceinline__ void count_draws(uint32_t key0, uint32_t key1, uint32_t window, uint32_t tet, int sp,
+                                            int m, DrawCounts& c) {
+  renew_s(key0, key1);  // the round keys are made here, not kept over the tile
+  for (int call = 0, left = m; left > 0; ++call, left -= 4) {
+    uint32_t x0 = (uint32_t)call, x1 = 1u + (uint32_t)sp, x2 = tet, x3 = window;
+    philox4x32_10(x0, x1, x2, x3, key0, key1);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t w = q == 0 ? x0 : (q == 1 ? x1 : (q == 2 ? x2 : x3));
+      const double u = (double)w;  // past the last draw: 2^33 or more, below no threshold
+      c.add(__hiloint2double(left > q ? __double2hiint(u) : 0x42000000, __double2loint(u)));
     }
-    const double p = item_p(V, it.sp, it.ln);
-    int trials = 0;
-    if (m > 0 && p > 0.0) {
-      if (m <= kSmallM) {
-        trials = m;
-        walked = m > it.npost;  // the cap may bind mid-walk
-      } else {
-        // the multinomial over the faces and staying, one binomial per stage
-        // from one call site, in stream order on this lane: stage k <= last
-        // gives face k Bin(rest, p s_k / (1 - p cum_{k-1})) of the molecules
-        // not yet placed (s_k the face's share, the last face present taking
-        // all that remains of p), the rest stay.  Should more leave than
-        // the post-reaction count (only a listed tet's item can), stages
-        // last + 1 .. 2 last split that count afresh by the shares (face k
-        // Bin(rest, s_k / (1 - cum_{k-1})), the last face the rest).
-        const int last = last_face(V.nbr[it.ln]);
-        const double2 g0 = V.geo0[it.ln], g1 = V.geo1[it.ln];
-        const int npost = it.npost;
-        int rest = m, n = 0;
-        double prev = 0.0;
-        bool capped = false;
-        int end = last;
+  }
+}
+
+// The part of an item before its plain draws: rounding draw, binomial faces
+// (into `split`), a walk under the cap (into c); leaves m, the draws still to
+// count.
+__device__ __forceinline__ void item_general(uint32_t key0, uint32_t key1, uint32_t window, uint32_t tet, int sp,
+                                             double nbar, int npost, const ItemGeo& g, DrawCounts& c, Faces& split,
+                                             int& m) {
+  renew_s(key0, key1);
+  Draw32 st(key0, key1, 1u + (uint32_t)sp, tet, window);
+  const double fl = floor(nbar);
+  const double frac = nbar - fl;
+  m = (int)fl;  // counts are int32
+  uint32_t rounding = 0;  // the stream's first word, if it went there
+  if (frac > 0.0) {
+    rounding = st.word();
+    if ((double)rounding * 0x1p-32 < frac) m += 1;
+  }
+  if (!(g.p > 0.0)) m = 0;
+  if (m > kSmallM) {
+    // the multinomial over the faces and staying, one binomial per stage
+    // from one call site, in stream order on this lane: stage k <= last
+    // gives face k Bin(rest, p s_k / (1 - p cum_{k-1})) of the molecules
+    // not yet placed (s_k the face's share, the last face present taking
+    // all that remains of p), the rest stay.  Should more leave than
+    // the post-reaction count (only after reactions), stages
+    // last + 1 .. 2 last split that count afresh by the shares (face k
+    // Bin(rest, s_k / (1 - cum_{k-1})), the last face the rest).
+    const int last = g.c0 == kAllFaces ? 0 : (g.c1 == kAllFaces ? 1 : (g.c2 == kAllFaces ? 2 : 3));
+    int rest = m, n = 0;
+    double prev = 0.0;
+    bool capped = false;
+    int end = last;
 #pragma unroll 1
-        for (int stage = 0; stage <= end; ++stage) {
-          const int f = capped ? stage - last - 1 : stage;
-          const double cum = (!capped && f == last) ? 1.0 : (f == 0 ? g0.y : (f == 1 ? g1.x : g1.y));
-          double qq;
-          if (!capped) {
-            // den is 0 only for p = 1 with the shares before face f summing to 1
-            const double den = 1.0 - p * prev;
-            qq = den > 0.0 ? (p * (cum - prev)) / den : (f == last ? 1.0 : 0.0);
-          } else {
-            qq = (cum - prev) / (1.0 - prev);
-          }
-          const int k = binom<int>(rest, qq, st);
-          X.face[f][lane] = (uint32_t)k;
-          rest -= k;
-          prev = cum;
-          if (!capped) {
-            n += k;
-            if (f == last && n > npost) {
-              capped = true;
-              end = last + last;
-              rest = npost;
-              prev = 0.0;
-            }
-          }
-        }
-        if (capped) X.face[last][lane] = (uint32_t)rest;
-#pragma unroll
-        for (int f = 0; f < 4; ++f)
-          if (f > last) X.face[f][lane] = 0u;
-        split = true;
+    for (int stage = 0; stage <= end; ++stage) {
+      const int f = capped ? stage - last - 1 : stage;
+      const double cum = (!capped && f == last) ? 1.0 : (f == 0 ? g.c0 : (f == 1 ? g.c1 : g.c2));
+      double qq;
+      if (!capped) {
+        // den is 0 only for p = 1 with the shares before face f summing to 1
+        const double den = 1.0 - g.p * prev;
+        qq = den > 0.0 ? (g.p * (cum - prev)) / den : (f == last ? 1.0 : 0.0);
+      } else {
+        qq = (cum - prev) / (1.0 - prev);
       }
-    }
-    const uint32_t w0 = used, nw = (uint32_t)trials;
-    if (nw > 0u && !walked) {
-      // at most five Philox calls (16 draws after the rounding draw): this
-      // lane makes them, comparing each uniform w 2^-32 with the item's
-      // probabilities as they are (the face counts fit a byte each)
-      const int last = last_face(V.nbr[it.ln]);
-      const double2 g0 = V.geo0[it.ln], g1 = V.geo1[it.ln];
-      // u = w 2^-32 < t exactly when w < t 2^32 (both scalings are exact), so
-      // the words are compared, as doubles, with the thresholds scaled once
-      const double ts = p * 0x1p32;
-      const double t0 = (p * g0.y) * 0x1p32, t1 = (p * g1.x) * 0x1p32, t2 = (p * g1.y) * 0x1p32;
-      for (uint32_t call = w0 >> 2; call <= (w0 + nw - 1u) >> 2; ++call) {
-        uint32_t x0 = call, x1 = 1u + (uint32_t)it.sp, x2 = tet, x3 = window;
-        philox4x32_10(x0, x1, x2, x3, key0, key1);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const uint32_t w = q == 0 ? x0 : (q == 1 ? x1 : (q == 2 ? x2 : x3));
-          const uint32_t idx = 4u * call + (uint32_t)q;
-          const double u = (double)w;
-          if (idx >= w0 && idx - w0 < nw && u < ts) {
-            const int f = (0 < last && u < t0) ? 0 : ((1 < last && u < t1) ? 1 : ((2 < last && u < t2) ? 2 : last));
-            own += 1u << (8 * f);
-          }
+      const int k = binom<int>(rest, qq, st);
+      split.o0 = f == 0 ? k : split.o0;
+      split.o1 = f == 1 ? k : split.o1;
+      split.o2 = f == 2 ? k : split.o2;
+      split.o3 = f == 3 ? k : split.o3;
+      rest -= k;
+      prev = cum;
+      if (!capped) {
+        n += k;
+        if (f == last && n > npost) {
+          capped = true;
+          end = last + last;
+          rest = npost;
+          prev = 0.0;
         }
       }
     }
-    if (walked) {  // in stream order, after the rounding draw
-      uint32_t th[4], full;
-      item_thresholds(V, it.ln, p, th, full);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) X.face[k][lane] = 0u;
-      int n = 0;
-      for (int j = 0; j < trials; ++j) {
-        const uint32_t w = st.word();
-        if (draw_leaves(w, th[3], full) && n < it.npost) {
-          X.face[draw_face(w, th[0], th[1], th[2], full)][lane] += 1u;
-          ++n;
-        }
-      }
+    if (capped) {
+      split.o0 = last == 0 ? rest : split.o0;
+      split.o1 = last == 1 ? rest : split.o1;
+      split.o2 = last == 2 ? rest : split.o2;
+      split.o3 = last == 3 ? rest : split.o3;
     }
+    m = 0;
+  } else if (m > npost) {  // the cap may bind mid-walk: in stream order
+    for (int j = 0; j < m; ++j) {
+      const double u = (double)st.word();
+      if (u < c.ts && c.ns < npost) c.add(u);
+    }
+    m = 0;
+  } else if (frac > 0.0 && m > 0) {
+    // the face draws start at the second word
+    c.take_back((double)rounding);
+    m += 1;
   }
-  ItemMoves r{0, 0, 0, 0, 0};
-  if (it.valid) {
-    uint32_t o[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) o[k] = ((own >> (8 * k)) & 0xffu) + (walked || split ? X.face[k][lane] : 0u);
-    r.o0 = (int)o[0];
-    r.o1 = (int)o[1];
-    r.o2 = (int)o[2];
-    r.o3 = (int)o[3];
-    r.n = r.o0 + r.o1 + r.o2 + r.o3;
-  }
-  return r;
-}
-
-// item_round for a round in which every item is a diffusion-only tet's
-// species with at most 16 molecules (mean occupancy = count = npost, so no
-// rounding draw, no binomial, no cap, words 0 .. m-1 of the stream): the
-// same draws and decisions as item_round's own-lane path, without its
-// set-up for the other cases.
-__device__ __forceinline__ ItemMoves item_round_small(uint32_t key0, uint32_t key1, uint32_t window,
-                                                     const ItemIn& it, const ItemView& V) {
-  uint32_t own = 0;  // leavers by face, a byte each
-  if (it.valid) {
-    const uint32_t tet = V.tet_of(it.ln);
-    const double p = item_p(V, it.sp, it.ln);
-    const uint32_t m = (uint32_t)it.npost;
-    if (p > 0.0) {
-      const int last = last_face(V.nbr[it.ln]);
-      const double2 g0 = V.geo0[it.ln], g1 = V.geo1[it.ln];
-      // the words against the thresholds scaled by 2^32 (exact, as above)
-      const double ps = p * 0x1p32;
-      const double t0 = (p * g0.y) * 0x1p32, t1 = (p * g1.x) * 0x1p32, t2 = (p * g1.y) * 0x1p32;
-      const uint32_t calls = (m + 3u) >> 2;
-      for (uint32_t call = 0; call < calls; ++call) {
-        uint32_t x0 = call, x1 = 1u + (uint32_t)it.sp, x2 = tet, x3 = window;
-        philox4x32_10(x0, x1, x2, x3, key0, key1);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const uint32_t w = q == 0 ? x0 : (q == 1 ? x1 : (q == 2 ? x2 : x3));
-          const double u = (double)w;
-          if (4u * call + (uint32_t)q < m && u < ps) {
-            const int f = (0 < last && u < t0) ? 0 : ((1 < last && u < t1) ? 1 : ((2 < last && u < t2) ? 2 : last));
-            own += 1u << (8 * f);
-          }
-        }
-      }
-    }
-  }
-  ItemMoves r;
-  r.o0 = (int)(own & 0xffu);
-  r.o1 = (int)((own >> 8) & 0xffu);
-  r.o2 = (int)((own >> 16) & 0xffu);
-  r.o3 = (int)(own >> 24);
-  r.n = r.o0 + r.o1 + r.o2 + r.o3;
-  return r;
 }
 
 // Tile schedule of a persistent block: the blocks are dispatched round-robin
@@ -687,35 +529,28 @@ __device__ __forceinline__ TileRange tile_range(int b, int G, int n_tiles) {
   return TileRange{lo + j, hi, Gx};
 }
 
-// The run a tile belongs to and what this step is for that run.
-struct TileCtx {
+// The run a tile belongs to and its first tet there; what the step is for the
+// run is read from its descriptor where it is used (scalar loads), so that a
+// tile in flight holds few registers.
+struct TileAt {
   cptr<RunDesc> rd;
-  int run;
-  int base;        // first tet of the tile, run-local
-  int T;
-  bool active;     // the run takes part in this step
-  uint32_t window; // run-local window index
-  double tau_k;
-  int32_t* cin;
-  int32_t* cout;
+  int base;
 };
 
-__device__ __forceinline__ TileCtx tile_ctx(const StepArgs& A, int tile, int k) {
+__device__ __forceinline__ TileAt tile_at(const StepArgs& A, int tile) {
   // with one run the tile map is (0, 64 t): no load on the chain to the counts
-  const int run = A.single_run ? 0 : as_const(reinterpret_cast<const int*>(A.tile_map))[2 * tile];
-  const int first = A.single_run ? tile * kWave : as_const(reinterpret_cast<const int*>(A.tile_map))[2 * tile + 1];
-  const cptr<RunDesc> rd = as_const(A.runs) + run;
-  TileCtx c;
-  c.rd = rd;
-  c.run = run;
-  c.base = first;
-  c.T = rd->T;
-  c.active = k < rd->n_steps;
-  c.window = rd->window0 + (uint32_t)k;
-  c.tau_k = k < rd->n_full ? rd->tau : rd->tau_last;
-  c.cin = rd->cnt[c.window & 1u];
-  c.cout = rd->cnt[(c.window + 1u) & 1u];
-  return c;
+  const cptr<int> map = as_const(reinterpret_cast<const int*>(A.tile_map));
+  const int run = A.single_run ? 0 : map[2 * tile];
+  const int first = A.single_run ? tile * kWave : map[2 * tile + 1];
+  return TileAt{as_const(A.runs) + run, first};
+}
+
+__device__ __forceinline__ bool run_active(cptr<RunDesc> rd, int k) { return k < rd->n_steps; }
+__device__ __forceinline__ uint32_t run_window(cptr<RunDesc> rd, int k) { return rd->window0 + (uint32_t)k; }
+__device__ __forceinline__ double run_tau(cptr<RunDesc> rd, int k) { return k < rd->n_full ? rd->tau : rd->tau_last; }
+// The counts window `window` of the run reads (0) and adds into (1).
+__device__ __forceinline__ int32_t* run_counts(cptr<RunDesc> rd, uint32_t window, uint32_t which) {
+  return rd->cnt[(window + which) & 1u];
 }
 
 // Everything one lane reads from global memory for its tet.
@@ -725,233 +560,344 @@ struct TetData {
   // selects a register rather than spilling the array to memory
   int __attribute__((ext_vector_type(SMAX))) N;
   double nav;
-  int4 nb;
-  double2 ga, gb;  // (G, cum0), (cum1, cum2)
   int reg;
 };
+struct TetGeo {
+  int4 nb;
+  double2 ga, gb;  // (G, cum0), (cum1, cum2)
+};
 
+// Row pointers are uniform (scalar registers) and end at the tile's first tet;
+// the lane's 32-bit offset is the only vector part of an address.
 template <int SMAX>
-__device__ __forceinline__ void load_tet(const TileCtx& c, int S, int i, TetData<SMAX>& d) {
-  const bool active = c.active && i < c.T;
+__device__ __forceinline__ void load_tet(const TileAt& at, int k, int S, int lane, TetData<SMAX>& d) {
+  const cptr<RunDesc> rd = at.rd;
+  const int T = rd->T;
+  const bool active = run_active(rd, k) && lane < T - at.base;
+  renew_s(S);
 #pragma unroll
-  for (int s = 0; s < SMAX; ++s) d.N[s] = (active && s < S) ? c.cin[(size_t)s * c.T + i] : 0;
+  for (int s = 0; s < SMAX; ++s) d.N[s] = 0;
   d.nav = 1.0;
+  d.reg = 0;
+  if (active) {
+    const uint32_t l = (uint32_t)lane;
+    const int32_t* row = run_counts(rd, run_window(rd, k), 0u) + at.base;
+#pragma unroll
+    for (int s = 0; s < SMAX; ++s) {
+      if (s < S) d.N[s] = row[l];
+      row += T;
+    }
+    d.nav = as_const(rd->nav + at.base)[l];
+    if (rd->region) d.reg = as_const(rd->region + at.base)[l];
+  }
+}
+__device__ __forceinline__ void load_geo(cptr<RunDesc> rd, int base, int lane, bool active, TetGeo& d) {
   d.nb = make_int4(-1, -1, -1, -1);
   d.ga = make_double2(0.0, 0.0);
   d.gb = make_double2(0.0, 0.0);
-  d.reg = 0;
   if (active) {
-    d.nav = as_const(c.rd->nav)[i];
-    d.nb = ld_int4(reinterpret_cast<const int4*>(c.rd->nbr), (size_t)i);
-    d.ga = ld_double2(reinterpret_cast<const double2*>(c.rd->geo), 2 * (size_t)i);
-    d.gb = ld_double2(reinterpret_cast<const double2*>(c.rd->geo), 2 * (size_t)i + 1);
-    if (c.rd->region) d.reg = as_const(c.rd->region)[i];
+    const uint32_t l = (uint32_t)lane;
+    d.nb = ld_int4(reinterpret_cast<const int4*>(rd->nbr) + base, l);
+    const double2* geo = reinterpret_cast<const double2*>(rd->geo) + 2 * (size_t)base;
+    d.ga = ld_double2(geo, 2u * l);
+    d.gb = ld_double2(geo, 2u * l + 1u);
   }
 }
 
-__device__ __forceinline__ unsigned long long* tally_slot(const StepArgs& A, int run) {
-  return as_const(A.runs)[run].tally + kTallyWords * (blockIdx.x & (kTallySlots - 1));
-}
-
-__device__ __forceinline__ int step_index(const StepArgs& A) {
-  return (A.step_base ? *as_const(A.step_base) : 0) + A.k_rel;
-}
-
-// What the detect kernel reads for one lane's tet.
+// Waits for the loads into d: without it the first use of the prefetched tile,
+// a tile later, waits for every atomic issued since (one counter holds loads
+// and atomics in order).
 template <int SMAX>
-struct TetCounts {
-  int __attribute__((ext_vector_type(SMAX))) N;  // a uniform species index selects a register
-  double nav;
-  int reg;
-};
-
-template <int SMAX>
-__device__ __forceinline__ void load_counts(const TileCtx& c, int S, int i, TetCounts<SMAX>& d) {
-  const bool active = c.active && i < c.T;
-#pragma unroll
-  for (int s = 0; s < SMAX; ++s) d.N[s] = (active && s < S) ? c.cin[(size_t)s * c.T + i] : 0;
-  d.nav = active ? as_const(c.rd->nav)[i] : 1.0;
-  d.reg = (active && c.rd->region) ? (int)as_const(c.rd->region)[i] : 0;
+__device__ __forceinline__ void settle(TetData<SMAX>& d) {
+  renew<SMAX>(d.N);
+  asm volatile("" : "+v"(d.nav), "+v"(d.reg));
 }
 
-// a_0 of one tet from the regrouped listing coefficients of its region (`lc`,
-// a scalar pointer when the run has one region, a per-lane one otherwise).
-// The terms are those of the reaction-by-reaction sum, so the result agrees
-// with it to within a few roundings (relative 1e-14 at most; fused
+__device__ __forceinline__ unsigned long long* tally_slot(cptr<RunDesc> rd) {
+  return rd->tally + kTallyWords * (blockIdx.x & (kTallySlots - 1));
+}
+
+// a_0 of one tet from the regrouped listing coefficients of a region (scalar
+// loads).  The terms are those of the reaction-by-reaction sum, so the result
+// agrees with it to within a few roundings (relative 1e-14 at most; fused
 // multiply-adds are fine here); it is only used with a margin far above that.
-template <int SMAX, typename P, typename NV>
-__device__ __forceinline__ double listing_rate(const StepArgs& A, P lc, const NV& N, double nav, double inv_nav) {
+template <int SMAX, typename NV>
+__device__ __forceinline__ double listing_rate(const StepArgs& A, cptr<double> lc, const NV& N, double nav) {
   // beta_s is zero for s >= S, and so are the counts there
   double lin = nav * lc[0];
 #pragma unroll
   for (int s = 0; s < SMAX; ++s) lin = __builtin_fma(lc[1 + s], (double)N[s], lin);
+  asm volatile("" : "+v"(lin));  // its coefficients are not held over the pairs
   double quad = 0.0;
+  // four pairs to a round of scalar loads (gamma is zero past the last pair)
 #pragma unroll 1
-  for (int p = 0; p < A.n_pairs; ++p) {
-    const int pr = A.pairs[p];
-    const int a = pr & 0xff, b = (pr >> 8) & 0xff;
-    const int x = a < SMAX ? N[a] : 0;
-    const int y = (b < SMAX ? N[b] : 0) - ((pr >> 16) & 1);
-    quad = __builtin_fma(lc[17 + p], (double)x * (double)y, quad);
-  }
-  return __builtin_fma(inv_nav, quad, lin);
-}
-
-// One block per tile by default (the grid may also be smaller: a block then
-// walks its tiles, the next tile's loads in flight while the current one is
-// worked on).
-template <int SMAX, int RMAX>
-__global__ void __launch_bounds__(kWave) window_detect_kernel(const StepArgs A) {
-  const int lane = threadIdx.x;
-  const int S = A.S;
-  const int k = step_index(A);
-  const int n_tiles = *as_const(A.n_tiles);
-  const TileRange tr = tile_range(blockIdx.x, gridDim.x, n_tiles);
-
-  TileCtx cc, nc;
-  TetCounts<SMAX> cur, nxt;
-  if (tr.first < tr.end) {
-    cc = tile_ctx(A, tr.first, k);
-    load_counts<SMAX>(cc, S, cc.base + lane, cur);
-  }
-  nc = cc;
-
-  for (int tile = tr.first; tile < tr.end; tile += tr.stride) {
-    const bool has_next = tile + tr.stride < tr.end;
-    const bool run_active = cc.active;
-    const cptr<RunDesc> rd = cc.rd;
-    const int i = cc.base + lane;
-    const bool active = i < cc.T;
-
-    // a_0 from the listing coefficients
-    const double nav = cur.nav;
-    const int reg = cur.reg;
-    const auto Nc = cur.N;
-    double a0 = 0.0;
-    if (run_active) {
-      const double inv_nav = 1.0 / nav;
-      if (rd->region == nullptr) a0 = listing_rate<SMAX>(A, as_const(rd->lcoef), Nc, nav, inv_nav);
-      else a0 = listing_rate<SMAX>(A, rd->lcoef + reg * kLStride, Nc, nav, inv_nav);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if (has_next) {
-      nc = tile_ctx(A, tile + tr.stride, k);
-      load_counts<SMAX>(nc, S, nc.base + lane, nxt);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-
-    // listing: the window's first SSA event falls inside [0, tau_k] only if
-    // t_reac = -ln(u) / a0 <= tau_k, and -ln(u) >= 1 - u; so a tet whose first
-    // uniform u of the window has 1 - u above a0 tau_k (with a relative
-    // margin of 1e-6, far above the rounding of a0, of ln and of the
-    // division) has no event, and every other tet with a0 > 0 is listed.  A
-    // listed tet without an event is harmless: its SSA ends at the first draw
-    // and its items are those of an unlisted tet.
-    bool event = false;
-    if (run_active && active && a0 > 0.0) {
-      Draw53 st(rd->key0, rd->key1, 0u, (uint32_t)i, cc.window);
-      const double u = st.oc();
-      event = !(1.0 - u > (cc.tau_k * a0) * 1.000001);
-    }
-    // binning by expected events: a listed tet with a0 tau_k above the
-    // threshold goes to the heavy bin, the others to the light bin, so that
-    // no event chunk runs light tets in lock-step with a long chain
-    const bool heavy = event && cc.tau_k * a0 > A.heavy_events;
-    const unsigned long long bh = __ballot(heavy), bl = __ballot(event && !heavy);
-    const int nh = (int)__popcll(bh), nl = (int)__popcll(bl);
-    if (lane == 0) {
-      A.wl_mask[tile] = bh | bl;
-      if (nh + nl) {
-        A.wl_tile_count[tile] = nh | (nl << 8);
-        // per bin, one atomic on the tile's sub-queue counts the queued tile
-        // (low word) and its listed tets (high word); the old low word is
-        // the tile's slot in that sub-queue
-        const int qj = tile & (kQueues - 1);
+  for (int p = 0; p < A.n_pairs; p += 4) {
 #pragma unroll
-        for (int bin = 0; bin < kBins; ++bin) {
-          const int nb = bin == 0 ? nh : nl;
-          if (nb) {
-            const unsigned long long old = atomicAdd(
-                A.evq_count + (((size_t)(k & 1) * kBins + bin) * kQueues + qj) * kQueueStride,
-                ((unsigned long long)nb << 32) | 1ull);
-            A.evq[((size_t)bin * kQueues + qj) * A.evq_cap + (size_t)(old & 0xffffffffull)] = tile;
-          }
-        }
-      }
+    for (int q = 0; q < 4; ++q) {
+      const int pr = A.pairs[p + q];
+      const int a = pr & 0xff, b = (pr >> 8) & 0xff;
+      const int x = a < SMAX ? N[a] : 0;
+      const int y = (b < SMAX ? N[b] : 0) - ((pr >> 16) & 1);
+      quad = __builtin_fma(lc[17 + p + q], (double)x * (double)y, quad);
     }
-    if (event) {  // the tile's listed tets take its own worklist slots, heavy first
-      const unsigned long long below = (1ull << lane) - 1ull;
-      const int pos = heavy ? (int)__popcll(bh & below) : nh + (int)__popcll(bl & below);
-      A.wl_tet[(size_t)tile * kWave + (size_t)pos] = i;
-    }
-    cc = nc;
-    cur = nxt;
   }
+  double r = __builtin_amdgcn_rcp(nav);  // one Newton step: to a few ulp
+  r = r * (2.0 - nav * r);
+  return __builtin_fma(quad, r, lin);
 }
 
-// LDS of the main kernel: a block is either a diffusion block or an event
-// block, so the two layouts share the space.
-template <int SMAX>
-struct DiffusionLds {
-  int acc[SMAX][kWave];         // counts, then next counts of own tets
-  double tauD[SMAX];            // tau_k D_s of the current run
-  uint32_t item[SMAX * kWave];  // packed items: count << 10 | lane << 4 | species
-  int4 nbr[kWave];
-  double2 geo[2][kWave];        // (G, cum0), (cum1, cum2)
-  ItemLds x;                    // the current round of items
-};
-
-// Lanes of an event chunk: the propensity table takes RMAX doubles per lane,
-// kept to 6 KiB.
-template <int RMAX>
-constexpr int chunk_width() {
-  return RMAX * 8 * kWave <= 6144 ? kWave : (RMAX * 8 * 32 <= 6144 ? 32 : 16);
+// Lanes that run the reaction operator of one tet: one per species, and one
+// per reaction or two.
+template <int SMAX, int RMAX>
+constexpr int ssa_lanes() {
+  return SMAX <= 4 && RMAX <= 8 ? 4 : (SMAX <= 8 && RMAX <= 16 ? 8 : 16);
 }
 
-template <int SMAX, int RMAX>
-struct EventLds {
-  static constexpr int CW = chunk_width<RMAX>();
-  // net changes and dependencies (copied whole from the device model) and
-  // the rate constants of the tile's run by region
-  uint32_t delta_w[32 * 16 / 4];        // int8 [32][16]
-  uint32_t deps_w[32 * 2];              // uint64 [32]: reactions whose propensity a reaction changes
-  uint32_t kc_w[kMaxRegions * 32 * 2];  // double [8][32]
-  union {
-    double a[RMAX][CW];                 // propensities of the chunk's tets, one column per lane
-    ItemLds x;                          // then the rounds of their diffusion items
-  };
-  double td[SMAX];                      // tau_k D_s of the tile's run
-  double nbar[kWave];                   // mean occupancy of the round's items
-  int npost[kWave];                     // post-reaction count of the round's items
-  uint16_t item[kWave];                 // the round's items: lane << 4 | species
-  int4 nbr[kWave];
-  double2 geo[2][kWave];                // (G, cum0), (cum1, cum2)
-  int tet[kWave];
+// A lane's reaction, as the propensity takes it (unpacked from the reaction
+// table once per block): lanes of the reactants in the group, what stands in
+// for an absent one, A + A.
+struct LaneReaction {
+  uint32_t info;  // s0 | s1 << 8 | order << 16, 0xff000000 if there is none
+  __device__ __forceinline__ void load(const StepArgs& A, int r) {
+    info = 0xff000000u;
+    if (r < A.R) {
+      const uint32_t i = (uint32_t)as_const(reinterpret_cast<const int*>(A.model))[offsetof(DevModel, info) / 4 + r];
+      info = ((i >> 8) & 0xffffu) | ((i & 0xffu) << 16);
+    }
+  }
 };
 
+// Items of changed species a tile holds at a time: a chunk of listed tets adds
+// up to 64 to what waits.
+constexpr int kDrawn = 96;
+
+// LDS of a block: this part, of one size in an instance ...
 template <int SMAX, int RMAX>
-union MainLds {
-  DiffusionLds<SMAX> d;
-  EventLds<SMAX, RMAX> e;
+struct TileLds {
+  // items of the species events changed: mean occupancy, post-reaction count,
+  // lane << 4 | species
+  double nbar[kDrawn];
+  int npost[kDrawn];
+  uint16_t drawn[kDrawn];
+  int8_t delta[RMAX][16];  // net changes by reaction and species
+  double tauD[SMAX];       // tau_k D_s of the current run
+  int4 nbr[kWave];        // neighbours, counted from the tile's first tet
+  double2 geo[2][kWave];  // (G, cum0), (cum1, cum2), kAllFaces from the last face on
 };
 
-// Diffusion blocks (b of G): the tets not listed, tile by tile, persistent,
-// the next tile's loads in flight while the current one is worked on.  With
-// `claim_only` (an event block done with its groups, b its XCD) the block has
-// no static tile and takes only claimed ones.
+// ... and what its size follows from the model's species count S, behind it:
+// the next counts of the tile's own tets, [S][64], and a space that holds first,
+// while listed tets run, a row of propensities per tet (and before them the
+// counts on the way to their lanes), then the items, count << 10 | lane << 4 |
+// species, [S * 64] at most.  Sized by S and not by SMAX, ten species take
+// 9.6 KB, and 16 blocks instead of 14 fit a CU.
+extern __shared__ __attribute__((aligned(16))) uint32_t tile_rows[];
+
 template <int SMAX, int RMAX>
-__device__ __forceinline__ void diffusion_part(const StepArgs& A, int k, int b, int G, DiffusionLds<SMAX>& L,
-                                               bool claim_only) {
+constexpr int ssa_row_bytes() {
+  return kWave / ssa_lanes<SMAX, RMAX>() * RMAX * (int)sizeof(double);
+}
+template <int SMAX, int RMAX>
+constexpr int tile_row_bytes(int S) {
+  constexpr int least = ssa_row_bytes<SMAX, RMAX>() > kWave * (int)sizeof(int) ? ssa_row_bytes<SMAX, RMAX>()
+                                                                               : kWave * (int)sizeof(int);
+  const int items = S * kWave * (int)sizeof(uint32_t);
+  return S * kWave * (int)sizeof(int) + (items > least ? items : least);
+}
+
+// The largest of the GL lanes' values, on all of them (butterfly within rows of
+// 16 lanes).
+template <int GL>
+__device__ __forceinline__ int group_max(int v) {
+  auto up = [&](int o) { v = o > v ? o : v; };
+  up(__builtin_amdgcn_mov_dpp(v, 0xb1, 0xf, 0xf, true));                  // quad_perm 1,0,3,2
+  up(__builtin_amdgcn_mov_dpp(v, 0x4e, 0xf, 0xf, true));                  // quad_perm 2,3,0,1
+  if (GL >= 8) up(__builtin_amdgcn_mov_dpp(v, 0x141, 0xf, 0xf, true));    // row_half_mirror
+  if (GL >= 16) up(__builtin_amdgcn_mov_dpp(v, 0x140, 0xf, 0xf, true));   // row_mirror
+  return v;
+}
+
+// The next GL calls of a listed tet's SSA stream, one a lane: -ln u and the
+// two uniforms.
+struct LaneDraws {
+  uint32_t first;  // the group's first call in hand
+  double mln, u01, u23;
+  __device__ __forceinline__ void refill(int j, uint32_t key0, uint32_t key1, uint32_t window, uint32_t tet,
+                                         uint32_t call) {
+    first = call;
+    renew_s(key0, key1);
+    uint32_t x0 = call + (uint32_t)j, x1 = 0u, x2 = tet, x3 = window;
+    philox4x32_10(x0, x1, x2, x3, key0, key1);
+    mln = -ln_basic(u53_oc(x0, x1));
+    u01 = u53_co(x0, x1);
+    u23 = u53_co(x2, x3);
+  }
+};
+
+__device__ __forceinline__ double lane_read(double v, int from) {
+  return __hiloint2double(__builtin_amdgcn_ds_bpermute(4 * from, __double2hiint(v)),
+                          __builtin_amdgcn_ds_bpermute(4 * from, __double2loint(v)));
+}
+
+// The reaction operator of up to 64 / GL tets over [0, tau], a tet to each
+// group of GL lanes (`run`: this lane's group has one): lane j of the group
+// holds species j (its count N, and as events change it its occupancy O, the
+// time t of the last change, and `touched`) and reactions j, j + GL.  Per
+// event: the waiting time and the composition draw come from one Philox call,
+// then one call per rejection attempt.  Returns the group's events.
+//
+// A tile lists a tet or two as a rule, and a step of one tet on one lane is a
+// chain of over a thousand instructions (every propensity, four scans of
+// them, the logarithm, a Philox call for each pair of draws).  Here the group
+// computes the propensities at once, and the next GL calls of the stream with
+// their logarithms; what has to go in reaction order, a_0 and a group's total,
+// are adds alone, of values read back from LDS.  A step of up to 4 tets (16
+// species and lanes a tet) is 2 us, with one tet on each lane of a wave it was
+// 5 us with the tables in LDS, and more with them spilled from registers.
+//
+// Composition: groups of reactions with equal binary exponent, visited from
+// the largest exponent down, picked with probability proportional to their
+// totals; rejection: a uniform member is accepted with probability a / 2^g.
+// Group totals are summed in reaction order.
+template <int SMAX, int RMAX>
+__device__ __forceinline__ unsigned int ssa_window(TileLds<SMAX, RMAX>& L, double* rows, bool run, uint32_t key0, uint32_t key1,
+                                                   uint32_t window, uint32_t tet, double tau, double nav, const double (&kc)[2],
+                                                   const LaneReaction (&lr)[2], int& N, double& O, double& t,
+                                                   bool& touched, int& err) {
+  constexpr int GL = ssa_lanes<SMAX, RMAX>();
+  constexpr int RPL = (RMAX + GL - 1) / GL;  // reactions of a lane
+  static_assert(RPL <= 2 && GL >= SMAX && GL <= 16, "a lane per species, at most two reactions a lane");
   const int lane = threadIdx.x;
-  const int S = A.S;
+  const int j = lane & (GL - 1), g0 = lane - j;
+  constexpr uint32_t group = (1u << GL) - 1u;
+  double* const a = rows + (size_t)(g0 / GL) * RMAX;
+  unsigned int events = 0;
+  if (run) {
+    double c[RPL];
+    const double inv_nav = 1.0 / nav;
+#pragma unroll
+    for (int q = 0; q < RPL; ++q) {
+      const int r = j + q * GL, order = (int)(lr[q].info >> 16);
+      const double f = order == 0 ? nav : (order == 1 ? 1.0 : inv_nav);
+      c[q] = order <= 2 && r < RMAX ? kc[q] * f : 0.0;
+    }
+    LaneDraws draws;
+    uint32_t call = 0;  // the next call
+    draws.refill(j, key0, key1, window, tet, call);
+    double dt = 0.0;
+    for (;;) {
+      double v[RPL];
+#pragma unroll
+      for (int q = 0; q < RPL; ++q) {
+        const int r = j + q * GL;
+        const int s0 = (int)(lr[q].info & 0xffu), s1 = (int)((lr[q].info >> 8) & 0xffu);
+        const int order = (int)(lr[q].info >> 16);
+        const bool same = order == 2 && s0 == s1;
+        const int xs = __builtin_amdgcn_ds_bpermute(4 * (g0 + (s0 & (GL - 1))), N);
+        const int ys = __builtin_amdgcn_ds_bpermute(4 * (g0 + (s1 & (GL - 1))), N);
+        v[q] = propensity(c[q], order == 0 ? 1 : xs, order == 2 ? ys - (same ? 1 : 0) : 1, same ? 0.5 : 1.0);
+        if (r < RMAX) a[r] = v[q];
+      }
+      if (call - draws.first >= (uint32_t)GL) draws.refill(j, key0, key1, window, tet, call);
+      const int at = g0 + (int)(call - draws.first);
+      const double mln = lane_read(draws.mln, at), u23 = lane_read(draws.u23, at);
+      wave_sync();
+      double a0 = 0.0;
+#pragma unroll
+      for (int r = 0; r < RMAX; ++r) a0 = a0 + a[r];
+      if (!(a0 > 0.0)) break;
+      const double t_reac = mln / a0;
+      if (dt + t_reac > tau) break;
+      ++call;
+      double left = u23 * a0;
+      int g = 0x7ff;  // exponent field of the group
+      uint32_t members = 0;
+      for (;;) {  // the groups from the largest exponent down
+        int e = 0;
+#pragma unroll
+        for (int q = 0; q < RPL; ++q) {
+          const int eq = exp_field(v[q]);
+          e = eq < g && eq > e ? eq : e;
+        }
+        e = group_max<GL>(e);
+        if (e == 0) break;  // none below: what is left falls to the last group
+        g = e;
+        members = 0;
+#pragma unroll
+        for (int q = 0; q < RPL; ++q)
+          members |= ((uint32_t)(__ballot(exp_field(v[q]) == g) >> g0) & group) << (q * GL);
+        double sum = 0.0;
+        for (uint32_t m = members; m != 0u; m &= m - 1u) sum = sum + a[__builtin_ctz(m)];
+        if (left < sum) break;
+        left = left - sum;
+      }
+      const double n = (double)__popc(members);
+      const double bound = __longlong_as_double((long long)(g + 1) << 52);
+      int rn = 0;
+      for (;;) {  // the attempts of all calls in hand at once; the first accepted one counts
+        int q = (int)(draws.u01 * n);
+        if ((double)q >= n) q = (int)n - 1;
+        uint32_t m = members;
+        for (; q > 0; --q) m &= m - 1u;
+        const int r = __builtin_ctz(m);
+        const bool accept = draws.first + (uint32_t)j >= call && draws.u23 * bound < a[r];
+        const uint32_t acc = (uint32_t)(__ballot(accept) >> g0) & group;
+        if (acc != 0u) {
+          const int w = __builtin_ctz(acc);
+          rn = __builtin_amdgcn_ds_bpermute(4 * (g0 + w), r);
+          call = draws.first + (uint32_t)w + 1u;
+          break;
+        }
+        call = draws.first + (uint32_t)GL;
+        draws.refill(j, key0, key1, window, tet, call);
+      }
+      dt = dt + t_reac;
+      const int d = (int)L.delta[rn][j];
+      int bad = 0;
+      if (d != 0) {
+        O = O + (double)N * (dt - t);
+        t = dt;
+        touched = true;
+        N += d;
+        if (N > kCountCap) bad |= kErrOverflow;
+      }
+      ++events;
+      if (events >= (unsigned int)kEventCap) bad |= kErrEvents;
+      err |= bad;
+      if (((uint32_t)(__ballot(bad != 0) >> g0) & group) != 0u) break;
+      wave_sync();
+    }
+  }
+  return events;
+}
+
+// Four waves per SIMD for up to 12 species, three above: the tiles are chains
+// of a lone wave and need the others to fill its gaps.  At three, 480,000 tets
+// of 10 species are 3 rounds of tiles and 46.1 us a window, at four 2 rounds
+// and 36.7 us (20 bytes of scratch a lane, outside the loops over items).
+// The larger tables would spill inside them at four.
+template <int SMAX, int RMAX>
+__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(SMAX <= 12 ? 4 : 3)))
+window_main_kernel(const StepArgs A) {
+  __shared__ TileLds<SMAX, RMAX> L;
+  int* const acc = reinterpret_cast<int*>(tile_rows);
+  uint32_t* const items = tile_rows + A.S * kWave;
+  const int k = A.step >= 0 ? A.step : as_const(A.step_words)[A.parity];
   const int n_tiles = *as_const(A.n_tiles);
+  const int b = blockIdx.x, G = gridDim.x;
+  if (b == 0) {
+    // the next window's step index and claim counters (nothing in this window
+    // reads the words of the other parity)
+    if (threadIdx.x == 0) A.step_words[(k + 1) & 1] = k + 1;
+    A.tile_ctr[((size_t)((k + 1) & 1) * 8 * kClaimSubs + (size_t)threadIdx.x) * kCtrStride] = 0;
+  }
   const TileRange tr = tile_range(b, G, n_tiles);
   // Run-time claiming (a launch-shape setting, for workloads whose tiles
   // differ in cost): the block's first tile is its static one, lo + j; the
   // tiles from lo + Gx on are cut into kClaimSubs sub-ranges (fewer if the
   // XCD has fewer blocks), each handed out in order by a counter of its own
   // to the blocks with j mod kClaimSubs equal to its index, each claim
-  // issued one tile ahead so that its latency hides behind a tile's work.
+  // issued a tile ahead so that its latency hides behind a tile's work.
   // Eight counters per XCD keep the claims at a window's start from queueing
   // on one address.  A block stops at its first claim past its sub-range,
   // so every block ends, and the slowest finishes within about one tile of
@@ -959,607 +905,355 @@ __device__ __forceinline__ void diffusion_part(const StepArgs& A, int k, int b, 
   const bool claim = A.tile_claim != 0 && G >= 8 && n_tiles >= 8;
   const int dyn0 = tr.first - (b >> 3) + tr.stride;  // lo + Gx
   const int nsub = tr.stride < kClaimSubs ? (tr.stride > 0 ? tr.stride : 1) : kClaimSubs;
-  const int sub = (claim_only ? (int)(blockIdx.x >> 3) : (b >> 3)) % nsub;
+  const int sub = (b >> 3) % nsub;
   int32_t* const ctr =
       A.tile_ctr + ((size_t)(k & 1) * 8 * kClaimSubs + (size_t)(b & 7) * kClaimSubs + (size_t)sub) * kCtrStride;
   const int n_claim = tr.end > dyn0 ? tr.end - dyn0 : 0;
   const int sub_lo = dyn0 + (int)(((long long)n_claim * sub) / nsub);
   const int sub_hi = dyn0 + (int)(((long long)n_claim * (sub + 1)) / nsub);
-  int first = tr.first;
-  if (claim_only) {
-    int r0 = 0;
-    if (lane == 0) r0 = atomicAdd(ctr, 1);
-    const int c0 = __builtin_amdgcn_readfirstlane(r0);
-    first = sub_lo + c0 < sub_hi ? sub_lo + c0 : tr.end;
-  }
-  int raw = 0;  // lane 0: the counter value of the claim in flight
-  if (claim && lane == 0) raw = atomicAdd(ctr, 1);
-  int cache_run = -1;
-  unsigned long long n_moved = 0, n_faces = 0;
-  uint32_t key0 = 0, key1 = 0, dmask = 0;  // per-run constants (uniform)
-
-  TileCtx cc, nc;
-  TetData<SMAX> cur, nxt;
-  unsigned long long cmask = 0, nmask = 0;  // listed tets of the tile
-  if (first < tr.end) {
-    cc = tile_ctx(A, first, k);
-    load_tet<SMAX>(cc, S, cc.base + lane, cur);
-    cmask = as_const(A.wl_mask)[first];
-  }
-  nc = cc;
-
-  for (int tile = first, next = 0; tile < tr.end; tile = next) {
-    if (claim) {
-      const int c = __builtin_amdgcn_readfirstlane(raw);
-      next = sub_lo + c < sub_hi ? sub_lo + c : tr.end;
-    } else {
-      next = tile + tr.stride;
+  constexpr int GL = ssa_lanes<SMAX, RMAX>();
+  {
+    const cptr<uint32_t> mw = as_const(reinterpret_cast<const uint32_t*>(A.model));
+    uint32_t* const dw = reinterpret_cast<uint32_t*>(L.delta);
+#pragma unroll
+    for (int j = 0; j < (RMAX * 4 + kWave - 1) / kWave; ++j) {
+      const int q = kWave * j + (int)threadIdx.x;
+      if (q < RMAX * 4) dw[q] = mw[offsetof(DevModel, delta) / 4 + q];
     }
-    const bool has_next = next < tr.end;
-    const bool run_active = cc.active;  // else the tile only forwards the prefetch
-    const cptr<RunDesc> rd = cc.rd;
-    const int T = cc.T;
-    const int i = cc.base + lane;
-    const bool active = i < T;
-    if (run_active && cc.run != cache_run) {
-      if (cache_run >= 0) {  // tallies are kept per run
-        const unsigned long long mv = wave_sum(n_moved), fm = wave_sum(n_faces);
-        if (lane == 0 && mv) atomicAdd(tally_slot(A, cache_run) + 1, mv);
-        if (lane == 0 && fm) atomicAdd(tally_slot(A, cache_run) + 2, fm);
-        n_moved = 0;
+  }
+  LaneReaction lr[2];
+  lr[0].load(A, (int)threadIdx.x & (GL - 1));
+  lr[1].load(A, ((int)threadIdx.x & (GL - 1)) + GL);
+  int raw = 0;  // lane 0: the counter value of the claim in flight
+  if (claim && threadIdx.x == 0) raw = atomicAdd(ctr, 1);
+  cptr<RunDesc> cached = nullptr;  // the run whose tables are in LDS
+  unsigned long long n_ev = 0, n_moved = 0;
+  uint32_t n_faces = 0;
+
+  TileAt here{nullptr, 0}, there{nullptr, 0};  // this tile, the next one
+  TetData<SMAX> cur, nxt;
+  if (tr.first < tr.end) {
+    here = tile_at(A, tr.first);
+    load_tet<SMAX>(here, k, A.S, threadIdx.x, cur);
+  }
+  int claimed = __builtin_amdgcn_readfirstlane(raw);
+
+  for (int tile = tr.first; tile < tr.end;) {
+    int lane = threadIdx.x, S = A.S;
+    asm volatile("" : "+v"(lane), "+s"(S));
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const cptr<RunDesc> rd = here.rd;
+    const int base = here.base;
+    const int T = rd->T;
+    const bool stepping = run_active(rd, k);  // else the tile only forwards the prefetch
+    const uint32_t window = run_window(rd, k);
+    const double tau = run_tau(rd, k);
+    const int i = base + lane;
+    const bool active = stepping && i < T;
+    if (stepping && rd != cached) {
+      if (cached != nullptr) {  // tallies are kept per run
+        const unsigned long long ev = wave_sum(n_ev), mv = wave_sum(n_moved), fm = wave_sum(n_faces);
+        if (lane == kWave - 1) {
+          if (ev) atomicAdd(tally_slot(cached), ev);
+          if (mv) atomicAdd(tally_slot(cached) + 1, mv);
+          if (fm) atomicAdd(tally_slot(cached) + 2, fm);
+        }
+        n_ev = n_moved = 0;
         n_faces = 0;
       }
-      key0 = rd->key0;
-      key1 = rd->key1;
       const double d = lane < S ? rd->D[lane < SMAX ? lane : 0] : 0.0;
-      if (lane < SMAX) L.tauD[lane] = lane < S ? cc.tau_k * d : 0.0;
-      dmask = (uint32_t)__ballot(lane < S && d > 0.0);
-      cache_run = cc.run;
+      if (lane < SMAX) L.tauD[lane] = tau * d;
+      cached = rd;
     }
-    // the tile's data moves from registers to LDS before the next tile's
-    // loads are issued, so that waiting for this tile's loads never waits for
-    // the next tile's (an inactive tile's data is all zero)
+    TetGeo tg;  // in flight until the listing is done
+    load_geo(rd, base, lane, active, tg);
+    const uint32_t key0 = rd->key0, key1 = rd->key1, dmask = rd->dmask;
+    const double nav = cur.nav;
+    const int reg = cur.reg;
+    auto N = cur.N;
+    int errbits = 0;
+    int most = 0;
 #pragma unroll
-    for (int s = 0; s < SMAX; ++s) L.acc[s][lane] = cur.N[s];
-    L.nbr[lane] = cur.nb;
-    L.geo[0][lane] = cur.ga;
-    L.geo[1][lane] = cur.gb;
-    const bool event = (cmask >> lane) & 1ull;
-    wave_sync();
-    __builtin_amdgcn_sched_barrier(0);
-    if (has_next) {
-      nc = tile_ctx(A, next, k);
-      load_tet<SMAX>(nc, S, nc.base + lane, nxt);
-      nmask = as_const(A.wl_mask)[next];
-      if (claim && lane == 0) raw = atomicAdd(ctr, 1);  // the tile after next
-    }
-    __builtin_amdgcn_sched_barrier(0);
+    for (int s = 0; s < SMAX; ++s) most = N[s] > most ? N[s] : most;
+    if (most > kCountCap) errbits |= kErrOverflow;
+    const bool any_wide = __ballot(most >= kPackedCount) != 0ull;
 
-    if (run_active) {
-      int n_own[SMAX];
-#pragma unroll
-      for (int s = 0; s < SMAX; ++s) n_own[s] = L.acc[s][lane];
-      const double Gl = L.geo[0][lane].x;
-
-      // a listed tet is left to the event blocks; for the others Nbar = N
-      uint32_t mask = 0;
-      if (active && !event && Gl > 0.0) {
-#pragma unroll
-        for (int s = 0; s < SMAX; ++s)
-          if (((dmask >> s) & 1u) && n_own[s] > 0) mask |= 1u << s;
+    // ---- listing ----
+    // The window's first SSA event falls inside [0, tau_k] only if
+    // t_reac = -ln(u) / a0 <= tau_k, and -ln(u) >= 1 - u; so a tet whose first
+    // uniform u of the window has 1 - u above a0 tau_k (with a relative
+    // margin of 1e-6, far above the rounding of a0, of ln and of the
+    // division) has no event, and every other tet with a0 > 0 is listed.  A
+    // listed tet without an event is harmless: its SSA ends at the first draw
+    // and its items are those of an unlisted tet.
+    bool event = false;
+    if (active) {
+      double a0 = 0.0;
+      if (rd->region == nullptr) {
+        a0 = listing_rate<SMAX>(A, as_const(rd->lcoef), N, nav);
+      } else {
+        // one region of the tile at a time (neighbouring tets mostly share one)
+        unsigned long long left = __ballot(true);
+        while (left != 0ull) {
+          const int q = __builtin_amdgcn_readlane(reg, __builtin_ctzll(left));
+          const double r = listing_rate<SMAX>(A, as_const(rd->lcoef) + q * kLStride, N, nav);
+          if (reg == q) a0 = r;
+          left &= ~__ballot(reg == q);
+        }
       }
-      // items in three classes, each species-major: more than 16 molecules
-      // (binomial face counts), so that few rounds wait on a binomial; then
-      // 5 to 16 (two to four Philox calls on the item's lane); then 1 to 4
-      // (one call).  A round's lanes step through as many calls as its
-      // longest item has, so grouping items by their number of calls keeps
-      // the short ones from idling behind the long ones.
-      int total = 0, errbits = 0;
-      const unsigned long long below = (1ull << lane) - 1ull;
-      uint32_t large = 0, multi = 0;  // species of this tet in the first two classes
+      if (a0 > 0.0) {
+        uint32_t w0 = 0u, w1 = 0u, w2 = (uint32_t)i, w3 = window;
+        philox4x32_10(w0, w1, w2, w3, key0, key1);
+        event = !(1.0 - u53_oc(w0, w1) > (tau * a0) * 1.000001);
+      }
+    }
+
+    const int last_f = last_face(tg.nb);
+    L.nbr[lane] = make_int4(tg.nb.x - base, tg.nb.y - base, tg.nb.z - base, tg.nb.w - base);
+    L.geo[0][lane] = make_double2(tg.ga.x, last_f > 0 ? tg.ga.y : kAllFaces);
+    L.geo[1][lane] = make_double2(last_f > 1 ? tg.gb.x : kAllFaces, last_f > 2 ? tg.gb.y : kAllFaces);
+    const bool coupled = tg.ga.x > 0.0;
+
+    // ---- diffusion operator ----
+    // The accumulator starts with what cannot leave: immobile species and tets
+    // without a neighbour.  (A listed tet's come after its events.)  From here
+    // on N holds what becomes an item.
+    const unsigned long long listed = __ballot(event);
+    const int n_listed = (int)__popcll(listed);
+    const bool apart = active && !coupled;
+    if (__ballot(apart) == 0ull) {
 #pragma unroll
       for (int s = 0; s < SMAX; ++s)
-        if ((mask >> s) & 1u) {
-          if (n_own[s] > kSmallM) large |= 1u << s;
-          else if (n_own[s] > 4) multi |= 1u << s;
-        }
-      const bool any_large = __ballot(large != 0u) != 0ull;  // uniform
-      const bool any_multi = __ballot(multi != 0u) != 0ull;
-#pragma unroll 1
-      for (int cls = 0; cls < 3; ++cls) {
-        if ((cls == 0 && !any_large) || (cls == 1 && !any_multi)) continue;
-        const uint32_t cm = cls == 0 ? large : (cls == 1 ? multi : mask & ~(large | multi));
-#pragma unroll
-        for (int s = 0; s < SMAX; ++s) {
-          const bool has = (cm >> s) & 1u;
-          const unsigned long long bs = __ballot(has);
-          if (has) {  // a count of 2^22 or more does not fit the packed field (0 marks it)
-            const int n = n_own[s];
-            L.item[total + __popcll(bs & below)] =
-                ((uint32_t)(n < (1 << 22) ? n : 0) << 10) | (uint32_t)(lane << 4) | (uint32_t)s;
-          }
-          total += (int)__popcll(bs);
-        }
-      }
+        if (s < S) acc[s * kWave + lane] = ((dmask >> s) & 1u) || event ? 0 : N[s];
+    } else {
 #pragma unroll
       for (int s = 0; s < SMAX; ++s) {
-        const int n = n_own[s];
-        if (n > kCountCap) errbits |= kErrOverflow;
-        // the accumulator starts with what cannot leave
-        L.acc[s][lane] = ((mask >> s) & 1u) || event || !active ? 0 : n;
+        if (s < S) acc[s * kWave + lane] = (((dmask >> s) & 1u) && !apart) || event ? 0 : N[s];
+        if (apart && !event) N[s] = 0;
+      }
+    }
+
+    // Rounds: the reaction operator of the listed tets, a few at a time; the
+    // items of the species their events changed wait for the tile's others,
+    // unless they are too many.
+    int c0 = 0, n_drawn = 0;
+    for (;;) {
+      while (c0 < n_listed && n_drawn <= kDrawn - kWave) {
+        // ---- reaction SSA operator over [0, tau_k] ----
+        const int rank = (int)__popcll(listed & below) - c0;
+        const bool mine = event && (unsigned)rank < (unsigned)(kWave / GL);
+        // the tets' counts go to their groups' lanes
+        int ln = lane;
+        renew(ln);
+        const int j = ln & (GL - 1), grp = ln / GL;
+        if (mine) {
+#pragma unroll
+          for (int s = 0; s < SMAX; ++s) items[rank * GL + s] = (uint32_t)N[s];
+          L.npost[n_drawn + rank] = lane;  // space not yet in use
+        }
+        wave_sync();
+        const bool run = c0 + grp < n_listed;
+        const int Lt = run ? L.npost[n_drawn + grp] : 0;
+        int Nj = run && j < SMAX ? (int)items[ln] : 0;
+        const double nav_t = lane_read(nav, Lt);
+        const int reg_t = __builtin_amdgcn_ds_bpermute(4 * Lt, reg);
+        const cptr<double> kw = as_const(rd->kcst) + reg_t * 32;
+        const double kc[2] = {j < RMAX ? kw[j] : 0.0, j + GL < RMAX ? kw[j + GL] : 0.0};
+        double O = 0.0, t = 0.0;
+        bool touched = false;
+        int err = 0;
+        const unsigned int events =
+            ssa_window<SMAX, RMAX>(L, reinterpret_cast<double*>(items), run, key0, key1, window, (uint32_t)(base + Lt), tau, nav_t, kc, lr, Nj,
+                                   O, t, touched, err);
+        errbits |= err;
+        if (j == 0) n_ev += events;
+        const unsigned long long bt = __ballot(touched);
+        const bool item = touched && ((dmask >> j) & 1u) && L.geo[0][Lt].x > 0.0;
+        const unsigned long long bi = __ballot(item);
+        wave_sync();
+        if (item) {
+          const int at = n_drawn + (int)__popcll(bi & below);
+          L.drawn[at] = (uint16_t)((Lt << 4) | j);
+          L.npost[at] = Nj;
+          L.nbar[at] = (O + (double)Nj * (tau - t)) / tau;
+        } else if (touched && Nj != 0) {
+          atomicAdd(acc + (j * kWave + Lt), Nj);
+        }
+        if (mine) {  // what is left of the tet: the species no event changed
+          const uint32_t changed = (uint32_t)(bt >> (rank * GL)) & ((1u << SMAX) - 1u);
+          int mobile = (int)dmask;
+          renew_s(mobile);
+#pragma unroll
+          for (int s = 0; s < SMAX; ++s) {
+            const bool gone = (changed >> s) & 1u;
+            if (!gone && (((mobile >> s) & 1) == 0 || apart) && N[s] != 0) atomicAdd(acc + (s * kWave + lane), N[s]);
+            if (gone || apart) N[s] = 0;
+          }
+        }
+        n_drawn += (int)__popcll(bi);
+        c0 += kWave / GL;
+        wave_sync();
+      }
+      const bool last = c0 >= n_listed;
+      int n_item = 0;
+      if (last) {
+        // the next tile's loads are in flight while the items are listed
+        __builtin_amdgcn_sched_barrier(0);
+        if (claim) tile = sub_lo + claimed < sub_hi ? sub_lo + claimed : tr.end;
+        else tile += tr.stride;
+        if (tile < tr.end) {
+          there = tile_at(A, tile);
+          load_tet<SMAX>(there, k, S, lane, nxt);
+          if (claim && lane == 0) raw = atomicAdd(ctr, 1);  // the tile after next
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // Items in five classes, each species-major: more than 16 molecules
+        // (binomial face counts), so that few rounds wait on a binomial; then
+        // those of four, three, two and one Philox calls (13 to 16, ... 1 to 4
+        // molecules).  A round's lanes step through as many calls as its
+        // longest item has: with 5 to 16 molecules in one class the dendrite
+        // made 18.8 calls a tile, of which its items need 12.
+        // Where no tet has more than four of any species there is one class,
+        // listed without the search for it.
+        renew<SMAX>(N);
+        if (__ballot(most > 4) == 0ull) {
+#pragma unroll
+          for (int s = 0; s < SMAX; ++s) {
+            const bool has = N[s] > 0 && ((dmask >> s) & 1u);
+            const unsigned long long bs = __ballot(has);
+            if (has) items[n_item + (int)__popcll(bs & below)] = (uint32_t)(N[s] << 10) | (uint32_t)(lane << 4) | (uint32_t)s;
+            n_item += (int)__popcll(bs);
+          }
+        } else {
+          uint32_t sets[5] = {0u, 0u, 0u, 0u, 0u};  // species with any item of a class or of one before it
+#pragma unroll
+          for (int s = 0; s < SMAX; ++s) {
+#pragma unroll
+            for (int cls = 0; cls < 5; ++cls)
+              sets[cls] |= __ballot(N[s] > kSmallM - 4 * cls) != 0ull ? 1u << s : 0u;
+          }
+#pragma unroll 1
+          for (int cls = 0; cls < 5; ++cls) {
+            const int lo = kSmallM - 4 * cls + 1;
+            const uint32_t span = cls == 0 ? 0x7fffffffu - (kSmallM + 1) : 3u;
+            uint32_t todo =
+                cls == 0 ? sets[0] : (cls == 1 ? sets[1] : (cls == 2 ? sets[2] : (cls == 3 ? sets[3] : sets[4])));
+            todo &= dmask;
+#pragma unroll 1
+            for (; todo != 0u; todo &= todo - 1u) {
+              const int s = __builtin_ctz(todo);
+              const int n = N[s];
+              const bool has = (uint32_t)(n - lo) <= span;
+              const unsigned long long bs = __ballot(has);
+              if (has)
+                items[n_item + (int)__popcll(bs & below)] =
+                    ((uint32_t)(n < kPackedCount ? n : 0) << 10) | (uint32_t)(lane << 4) | (uint32_t)s;
+              n_item += (int)__popcll(bs);
+            }
+          }
+        }
+        settle<SMAX>(nxt);
+        claimed = __builtin_amdgcn_readfirstlane(raw);
       }
       wave_sync();
-
-      const int base = cc.base;
-      const ItemView view{L.nbr, L.geo[0], L.geo[1], L.tauD, nullptr, base};
+      const int total = n_drawn + n_item;
+      int32_t* const out = run_counts(rd, window, 1u);
       for (int r0 = 0; r0 < total; r0 += kWave) {
-        ItemIn in;
-        in.valid = lane < total - r0;
+        const int at = r0 + lane;
+        const bool valid = at < total;
         int Ln = 0, sp = 0, m = 0;
-        int4 tnb = make_int4(-1, -1, -1, -1);
-        if (in.valid) {
-          const uint32_t itw = L.item[r0 + lane];
+        double nb = 0.0;
+        bool general = false;  // uniform
+        if (r0 < n_drawn) {    // a round with items of changed species
+          general = true;
+          if (valid) {
+            const uint32_t itw = at < n_drawn ? (uint32_t)L.drawn[at] : items[at - n_drawn];
+            Ln = (int)((itw >> 4) & 63);
+            sp = (int)(itw & 15);
+            m = at < n_drawn ? L.npost[at] : (int)(itw >> 10);
+            nb = at < n_drawn ? L.nbar[at] : 0.0;
+          }
+        } else if (valid) {
+          const uint32_t itw = items[at - n_drawn];
           Ln = (int)((itw >> 4) & 63);
           sp = (int)(itw & 15);
           m = (int)(itw >> 10);
-          tnb = L.nbr[Ln];
         }
-        // A count of 2^22 or more does not fit the packed field (0 marks
-        // it): its lane reads it from the count buffer, in a rare uniform
-        // branch that hands the value on through LDS.  Any later use of a
-        // register still awaiting a global load would otherwise make the
-        // whole round wait on the vector-memory counter, i.e. for the next
-        // tile's loads and this tile's atomics as well.
-        if (__ballot(in.valid && m == 0) != 0ull) {
-          if (in.valid && m == 0) L.item[r0 + lane] = (uint32_t)cc.cin[(size_t)sp * T + base + Ln];
-          wave_sync();
-          if (in.valid && m == 0) m = (int)L.item[r0 + lane];
+        const bool plain = valid && at >= n_drawn;
+        if (any_wide) {  // a count that does not fit its field is read from the count buffer
+          if (plain && m == 0) m = run_counts(rd, window, 0u)[(size_t)sp * T + base + Ln];
         }
-        in.sp = sp;
-        in.ln = Ln;
-        in.nbar = (double)m;
-        in.npost = m;
-        const bool big_round = __ballot(in.valid && m > kSmallM) != 0ull;  // uniform
-        const ItemMoves mv = big_round ? item_round(key0, key1, cc.window, in, view, L.x)
-                                       : item_round_small(key0, key1, cc.window, in, view);
-        if (in.valid) {
+        if (plain) nb = (double)m;
+        general = general || __ballot(m > kSmallM) != 0ull;
+        if (valid) {
+          const int4 tnb = L.nbr[Ln];
+          const double2 g0 = L.geo[0][Ln], g1 = L.geo[1][Ln];
+          const ItemGeo geo{fmin(L.tauD[sp] * g0.x, 1.0), g0.y, g1.x, g1.y};
+          const uint32_t tet = (uint32_t)(base + Ln);
+          int draws = m;
+          DrawCounts c(geo);
+          Faces o{0, 0, 0, 0};
+          if (general) item_general(key0, key1, window, tet, sp, nb, m, geo, c, o, draws);
+          count_draws(key0, key1, window, tet, sp, draws, c);
+          const Faces d = c.faces();
+          if (general) o = Faces{o.o0 + d.o0, o.o1 + d.o1, o.o2 + d.o2, o.o3 + d.o3};
+          else o = d;
           // own remainder and moves to the tile's own tets go to LDS, the
           // rest to the next count buffer
-          int32_t* __restrict__ out_s = cc.cout + (size_t)sp * T;
-          if (m != mv.n) atomicAdd(&L.acc[sp][Ln], m - mv.n);
-#define RDX_DEPOSIT(t, v)                                               \
-          if (v) {                                                      \
-            const unsigned off = (unsigned)((t) - base);                 \
-            if (off < (unsigned)kWave) atomicAdd(&L.acc[sp][off], (v));  \
-            else atomicAdd(out_s + (t), (v));                            \
-            ++n_faces;                                                   \
+          const int n = o.o0 + o.o1 + o.o2 + o.o3;
+          int* const own = acc + sp * kWave;
+          int32_t* const row = out + ((size_t)sp * T + base);
+          if (m != n) atomicAdd(own + Ln, m - n);
+#define RDX_DEPOSIT(t, v)                                              \
+          if (v) {                                                     \
+            if ((unsigned)(t) < (unsigned)kWave) atomicAdd(own + (t), (v)); \
+            else atomicAdd(row + (t), (v));                            \
+            ++n_faces;                                                 \
           }
-          RDX_DEPOSIT(tnb.x, mv.o0)
-          RDX_DEPOSIT(tnb.y, mv.o1)
-          RDX_DEPOSIT(tnb.z, mv.o2)
-          RDX_DEPOSIT(tnb.w, mv.o3)
+          RDX_DEPOSIT(tnb.x, o.o0)
+          RDX_DEPOSIT(tnb.y, o.o1)
+          RDX_DEPOSIT(tnb.z, o.o2)
+          RDX_DEPOSIT(tnb.w, o.o3)
 #undef RDX_DEPOSIT
-          n_moved += (unsigned long long)mv.n;
+          n_moved += (unsigned long long)n;
         }
+        wave_sync();
       }
-      wave_sync();
-      // coalesced flush of the tile's own tets (other tiles add into them too)
-      int v[SMAX];
-#pragma unroll
-      for (int s = 0; s < SMAX; ++s) v[s] = L.acc[s][lane];
+      n_drawn = 0;
+      if (last) break;
+    }
+    if (stepping) {
+      // coalesced flush of the tile's own tets (other tiles add into them too);
+      // the counts read are cleared for the window after next
+      renew_s(S);
       if (active) {
+        const uint32_t l = (uint32_t)lane;
+        int32_t *in = run_counts(rd, window, 0u) + base, *out = run_counts(rd, window, 1u) + base;
 #pragma unroll
         for (int s = 0; s < SMAX; ++s) {
           if (s < S) {
-            if (v[s] != 0) atomicAdd(cc.cout + (size_t)s * T + i, v[s]);
-            // the target of the window after next (a listed tet's counts are
-            // read and cleared by its event block)
-            if (!event) cc.cin[(size_t)s * T + i] = 0;
+            const int v = acc[s * kWave + lane];
+            if (v != 0) atomicAdd(out + l, v);
+            in[l] = 0;
           }
+          in += T;
+          out += T;
         }
       }
       if (errbits) atomicOr(rd->err, errbits);
     }
     wave_sync();  // LDS is rebuilt for the next tile
-    cc = nc;
+    here = there;
     cur = nxt;
-    cmask = nmask;
   }
 
-  const unsigned long long mv = wave_sum(n_moved), fm = wave_sum(n_faces);
-  if (lane == 0 && cache_run >= 0 && mv) atomicAdd(tally_slot(A, cache_run) + 1, mv);
-  if (lane == 0 && cache_run >= 0 && fm) atomicAdd(tally_slot(A, cache_run) + 2, fm);
-}
-
-// One event chunk: up to CW listed tets of one run (worklist slot `slot` on
-// the lanes below `n_work`; `tile0` gives the run), one per lane: the SSA
-// window, the occupancies, then the diffusion of their items.  `tables`,
-// `cache_run` and `dmask` carry what is already in LDS from the previous
-// chunk of the block.
-template <int SMAX, int RMAX>
-__device__ __forceinline__ void event_chunk(const StepArgs& A, int k, int tile0, int n_work, size_t slot,
-                                            EventLds<SMAX, RMAX>& L, bool& tables, int& cache_run,
-                                            uint32_t& dmask) {
-  constexpr int CW = EventLds<SMAX, RMAX>::CW;
-  const int lane = threadIdx.x;
-  const int S = A.S, R = A.R;
-  {
-    const TileCtx cc = tile_ctx(A, tile0, k);
-    const cptr<RunDesc> rd = cc.rd;
-    const int T = cc.T;
-    const double tau = cc.tau_k;
-
-    // the worklist entry names the tet; its counts, N_A V, region,
-    // neighbours and couplings are read in place (the diffusion blocks leave
-    // a listed tet's counts alone), then its counts are cleared for the
-    // window after next
-    const bool active = lane < n_work;
-    int N[SMAX];
-    int i = 0;
-    double nav = 1.0;
-    int4 nb = make_int4(-1, -1, -1, -1);
-    double2 ga = make_double2(0.0, 0.0), gb = make_double2(0.0, 0.0);
-    if (active) i = A.wl_tet[slot];
-#pragma unroll
-    for (int s = 0; s < SMAX; ++s) N[s] = (active && s < S) ? cc.cin[(size_t)s * T + i] : 0;
-    if (active) {
-      nav = as_const(rd->nav)[i];
-      nb = ld_int4(reinterpret_cast<const int4*>(rd->nbr), (size_t)i);
-      ga = ld_double2(reinterpret_cast<const double2*>(rd->geo), 2 * (size_t)i);
-      gb = ld_double2(reinterpret_cast<const double2*>(rd->geo), 2 * (size_t)i + 1);
-    }
-    // tables and per-run constants: every load issued before any is used
-    const bool need_tables = !tables, need_run = cc.run != cache_run;
-    const bool regions = rd->region != nullptr;
-    const cptr<uint32_t> mw = as_const(reinterpret_cast<const uint32_t*>(A.model));
-    const cptr<uint32_t> kw = as_const(reinterpret_cast<const uint32_t*>(rd->kcst));
-    uint32_t d0 = 0, d1 = 0, dp = 0, kv[kMaxRegions];
-    double dv = 0.0;
-    int reg = 0;
-    if (need_tables) {
-      d0 = mw[offsetof(DevModel, delta) / 4 + lane];
-      d1 = mw[offsetof(DevModel, delta) / 4 + kWave + lane];
-      dp = mw[offsetof(DevModel, deps) / 4 + lane];
-    }
-    if (need_run) {
-#pragma unroll
-      for (int q = 0; q < kMaxRegions; ++q) kv[q] = (q == 0 || regions) ? kw[q * kWave + lane] : 0u;
-      if (lane < SMAX && lane < S) dv = rd->D[lane];
-    }
-    if (active && regions) reg = as_const(rd->region)[i];
-    if (need_tables) {
-      L.delta_w[lane] = d0;
-      L.delta_w[kWave + lane] = d1;
-      L.deps_w[lane] = dp;
-      tables = true;
-    }
-    if (need_run) {
-#pragma unroll
-      for (int q = 0; q < kMaxRegions; ++q)
-        if (q == 0 || regions) L.kc_w[q * kWave + lane] = kv[q];
-      if (lane < SMAX) L.td[lane] = lane < S ? tau * dv : 0.0;
-      dmask = (uint32_t)__ballot(lane < SMAX && lane < S && tau * dv > 0.0);
-      cache_run = cc.run;
-    }
-    wave_sync();
-    const double(*s_kc)[32] = reinterpret_cast<const double(*)[32]>(L.kc_w);
-
-    // the tet's neighbours and couplings wait in LDS while the SSA runs
-    L.tet[lane] = i;
-    L.nbr[lane] = nb;
-    L.geo[0][lane] = ga;
-    L.geo[1][lane] = gb;
-
-    unsigned long long n_ev = 0, n_mv = 0, n_fm = 0;
-    int errbits = 0;
-    uint32_t mask = 0;
-    double nbv[SMAX];  // mean occupancies of the tet's items
-    int npv[SMAX];     // post-reaction counts
-    if (active) {
-      // counts as one vector value (uniform species indices select
-      // registers); rate constants of the tet's region from LDS
-      int __attribute__((ext_vector_type(SMAX))) Nv;
-#pragma unroll
-      for (int s = 0; s < SMAX; ++s) Nv[s] = N[s];
-      const double inv_nav = 1.0 / nav;
-      const double* kreg = s_kc[reg];
-      double* col = &L.a[0][lane];  // a_r at col[r * CW]
-#pragma unroll 1
-      for (int r = 0; r < R; ++r) col[r * CW] = propensity<SMAX>(A.info[r], kreg[r], Nv, nav, inv_nav);
-      // the counts are in registers now; clear them for the window after next
-#pragma unroll
-      for (int s = 0; s < SMAX; ++s)
-        if (s < S) cc.cin[(size_t)s * T + i] = 0;
-
-      // ---- reaction SSA operator over [0, tau_k] ----
-      double O[SMAX], tS[SMAX];
-#pragma unroll
-      for (int s = 0; s < SMAX; ++s) {
-        O[s] = 0.0;
-        tS[s] = 0.0;
-      }
-      uint32_t touched = 0;
-      Draw53 st(rd->key0, rd->key1, 0u, (uint32_t)i, cc.window);
-      double dt = 0.0;
-      unsigned int ev_tet = 0;
-      for (;;) {
-        double a0 = 0.0;
-#pragma unroll 4
-        for (int r = 0; r < R; ++r) a0 = a0 + col[r * CW];
-        if (!(a0 > 0.0)) break;
-        const double u = st.oc();
-        const double t_reac = -ln_basic(u) / a0;
-        if (dt + t_reac > tau) break;
-        const int rn = cr_select_col(col, CW, R, a0, st);
-        dt = dt + t_reac;
-        // few lanes of a wave are in the loop at a time, so branches that
-        // skip unchanged species and unaffected reactions are cheap
-        const uint4 drow = reinterpret_cast<const uint4*>(L.delta_w)[rn];
-        const unsigned long long dep = reinterpret_cast<const unsigned long long*>(L.deps_w)[rn];
-#pragma unroll
-        for (int s = 0; s < SMAX; ++s) {
-          if (s < S) {
-            const uint32_t wd = (s >> 2) == 0 ? drow.x : ((s >> 2) == 1 ? drow.y : ((s >> 2) == 2 ? drow.z : drow.w));
-            const int d = (int)(int8_t)((wd >> (8 * (s & 3))) & 0xffu);
-            if (d != 0) {
-              const int n = Nv[s];
-              O[s] = O[s] + (double)n * (dt - tS[s]);
-              tS[s] = dt;
-              touched |= 1u << s;
-              Nv[s] = n + d;
-              if (n + d > kCountCap) errbits |= kErrOverflow;
-            }
-          }
-        }
-        // the propensities that read a changed species
-#pragma unroll 1
-        for (int r = 0; r < R; ++r)
-          if ((dep >> r) & 1ull) col[r * CW] = propensity<SMAX>(A.info[r], kreg[r], Nv, nav, inv_nav);
-        ++ev_tet;
-        if (errbits) break;
-        if (ev_tet >= (unsigned int)kEventCap) {
-          errbits |= kErrEvents;
-          break;
-        }
-      }
-      n_ev = ev_tet;
-
-      // ---- mean occupancies; items for the diffusion operator ----
-      const bool coupled = L.geo[0][lane].x > 0.0;
-#pragma unroll
-      for (int s = 0; s < SMAX; ++s) {
-        nbv[s] = 0.0;
-        npv[s] = 0;
-        if (s >= S) continue;
-        const int n = Nv[s];
-        const double occ = (O[s] + (double)n * (tau - tS[s])) / tau;
-        const double nbar = ((touched >> s) & 1u) ? occ : (double)n;
-        if (((dmask >> s) & 1u) && coupled && nbar > 0.0) {
-          mask |= 1u << s;
-          nbv[s] = nbar;
-          npv[s] = n;
-        } else if (n != 0) {
-          atomicAdd(cc.cout + (size_t)s * T + i, n);  // nothing can leave
-        }
-      }
-    } else {
-#pragma unroll
-      for (int s = 0; s < SMAX; ++s) {
-        nbv[s] = 0.0;
-        npv[s] = 0;
-      }
-    }
-    const int cnt = __popc(mask);
-    const int incl = wave_inclusive_scan(cnt);
-    const int total = __shfl(incl, kWave - 1);
-    const int first = incl - cnt;
-    const ItemView view{L.nbr, L.geo[0], L.geo[1], L.td, L.tet, 0};
-    // items in rounds of 64: each lane parks the items of the round that
-    // are its own, then every lane samples one
-    for (int r0 = 0; r0 < total; r0 += kWave) {
-      int pos = first;
-#pragma unroll
-      for (int s = 0; s < SMAX; ++s) {
-        if ((mask >> s) & 1u) {
-          const unsigned slot = (unsigned)(pos - r0);
-          if (slot < (unsigned)kWave) {
-            L.item[slot] = (uint16_t)((lane << 4) | s);
-            L.nbar[slot] = nbv[s];
-            L.npost[slot] = npv[s];
-          }
-          ++pos;
-        }
-      }
-      wave_sync();
-      ItemIn in;
-      in.valid = lane < total - r0;
-      int sp = 0, ti = 0, npost = 0, Ln = 0;
-      double nbar = 0.0;
-      int4 tnb = make_int4(-1, -1, -1, -1);
-      if (in.valid) {
-        const int it = L.item[lane];
-        Ln = it >> 4;
-        sp = it & 15;
-        ti = L.tet[Ln];
-        npost = L.npost[lane];
-        nbar = L.nbar[lane];
-        tnb = L.nbr[Ln];
-      }
-      in.sp = sp;
-      in.ln = Ln;
-      in.nbar = nbar;
-      in.npost = npost;
-      const ItemMoves mv = item_round(rd->key0, rd->key1, cc.window, in, view, L.x);
-      if (in.valid) {
-        int32_t* out_s = cc.cout + (size_t)sp * T;
-        if (npost != mv.n) atomicAdd(out_s + ti, npost - mv.n);
-        if (mv.o0) atomicAdd(out_s + tnb.x, mv.o0);
-        if (mv.o1) atomicAdd(out_s + tnb.y, mv.o1);
-        if (mv.o2) atomicAdd(out_s + tnb.z, mv.o2);
-        if (mv.o3) atomicAdd(out_s + tnb.w, mv.o3);
-        n_mv += (unsigned long long)mv.n;
-        n_fm += (unsigned long long)((mv.o0 != 0) + (mv.o1 != 0) + (mv.o2 != 0) + (mv.o3 != 0));
-      }
-      wave_sync();  // the round's LDS entries are rebuilt for the next
-    }
-    const unsigned long long ev_sum = wave_sum(n_ev), mv_sum = wave_sum(n_mv), fm_sum = wave_sum(n_fm);
-    if (lane == 0) {
-      if (ev_sum) atomicAdd(tally_slot(A, cc.run), ev_sum);
-      if (mv_sum) atomicAdd(tally_slot(A, cc.run) + 1, mv_sum);
-      if (fm_sum) atomicAdd(tally_slot(A, cc.run) + 2, fm_sum);
-    }
-    if (errbits) atomicOr(rd->err, errbits);
-    wave_sync();  // LDS is rebuilt for the next chunk
+  const unsigned long long ev = wave_sum(n_ev), mv = wave_sum(n_moved), fm = wave_sum(n_faces);
+  if (threadIdx.x == kWave - 1 && cached != nullptr) {
+    if (ev) atomicAdd(tally_slot(cached), ev);
+    if (mv) atomicAdd(tally_slot(cached) + 1, mv);
+    if (fm) atomicAdd(tally_slot(cached) + 2, fm);
   }
 }
-
-// The queue of one bin, as the main kernel reassembles it: lane j holds its
-// sub-queue j's inclusive prefix of queued tiles.
-struct BinQueue {
-  int n_queued;  // queued tiles of the bin
-  int K;         // queued tiles per group
-  int n_groups;
-  int q_incl;    // per lane
-};
-
-// Event blocks (b of E): groups of K consecutive queue entries of a bin,
-// group b, b + E, ... over the heavy bin's groups and then the light bin's;
-// the listed tets of a group's tiles are packed CW to a chunk (a chunk holds
-// one run and one bin), so that tiles with one or two listed tets share one
-// pass of the SSA, and tets expected to have several events share chunks
-// with each other only.
-template <int SMAX, int RMAX>
-__device__ __forceinline__ void event_part(const StepArgs& A, int k, int b, int E, const BinQueue* Q,
-                                           EventLds<SMAX, RMAX>& L) {
-  constexpr int CW = EventLds<SMAX, RMAX>::CW;
-  const int lane = threadIdx.x;
-  bool tables = false;
-  int cache_run = -1;
-  uint32_t dmask = 0;  // species with tau_k D_s > 0 in the cached run
-  const cptr<int> tile_run = as_const(reinterpret_cast<const int*>(A.tile_map));
-  const int n_groups = Q[0].n_groups + Q[1].n_groups;
-
-  for (int gg = b; gg < n_groups; gg += E) {
-    const int bin = gg < Q[0].n_groups ? 0 : 1;
-    const BinQueue& B = Q[bin];
-    const int g = gg - (bin ? Q[0].n_groups : 0);
-    const int* evq = A.evq + (size_t)bin * kQueues * A.evq_cap;
-    // the group's tiles, listed counts and runs: lane j loads entry j (one
-    // round of loads for the whole group)
-    const int q0 = g * B.K;
-    const int nq = B.n_queued - q0 < B.K ? B.n_queued - q0 : B.K;
-    // entry q is slot q - (tiles of the sub-queues before j) of sub-queue j,
-    // j the first sub-queue whose inclusive prefix exceeds q
-    int g_tile = 0, g_n = 0, g_first = 0, g_run = -1;
-    for (int l = 0; l < nq; ++l) {
-      const int q = q0 + l;
-      const int j = (int)__popcll(__ballot(B.q_incl <= q));
-      const int before = j > 0 ? __builtin_amdgcn_readlane(B.q_incl, j - 1) : 0;
-      if (lane == l) g_tile = evq[(size_t)j * A.evq_cap + (size_t)(q - before)];
-    }
-    if (lane < nq) {
-      // the bin's listed tets of the tile and their first worklist slot
-      // (heavy tets first)
-      const int c = A.wl_tile_count[g_tile];
-      g_n = bin == 0 ? (c & 0xff) : (c >> 8);
-      g_first = bin == 0 ? 0 : (c & 0xff);
-      g_run = A.single_run ? 0 : tile_run[2 * g_tile];
-    }
-    // walk the group's tiles and their listed tets in order; the chunk is
-    // run from one place in the code
-    int q = -1, tile = 0, n = 0, first = 0, run = -1, j0 = 0;
-    int fill = 0, tile0 = 0, run0 = -1;
-    size_t slot = 0;
-    for (;;) {
-      if (j0 >= n) {  // the next tile of the group with listed tets
-        j0 = 0;
-        n = 0;
-        for (++q; q < nq; ++q) {
-          n = __builtin_amdgcn_readlane(g_n, q);
-          if (n > 0) break;
-        }
-        if (q < nq) {
-          tile = __builtin_amdgcn_readlane(g_tile, q);
-          first = __builtin_amdgcn_readlane(g_first, q);
-          run = __builtin_amdgcn_readlane(g_run, q);
-        }
-      }
-      const bool done = q >= nq;
-      if (fill > 0 && (done || run != run0 || fill == CW)) {
-        event_chunk<SMAX, RMAX>(A, k, tile0, fill, slot, L, tables, cache_run, dmask);
-        fill = 0;
-      }
-      if (done) break;
-      if (fill == 0) {
-        tile0 = tile;
-        run0 = run;
-      }
-      const int take = n - j0 < CW - fill ? n - j0 : CW - fill;
-      if (lane >= fill && lane < fill + take) slot = (size_t)tile * kWave + (size_t)(first + j0 + lane - fill);
-      fill += take;
-      j0 += take;
-    }
-  }
-}
-
-// Three waves per SIMD: the diffusion blocks need the occupancy to hide
-// their load latency, so the compiler keeps the event part (the larger
-// register footprint) within that budget, spilling if it must.
-template <int SMAX, int RMAX>
-__global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(3)))
-window_main_kernel(const StepArgs A) {
-  __shared__ MainLds<SMAX, RMAX> lds;
-  const int k = step_index(A);
-  // the sub-queues of each bin: lane j holds sub-queue j's tiles and their
-  // inclusive prefix sum over the sub-queues
-  const int lane = threadIdx.x;
-  const int G = gridDim.x;
-  const int K_max = A.ev_group_max >= 1 ? A.ev_group_max : 1;
-  BinQueue Q[kBins];
-  int n_groups = 0;
-#pragma unroll
-  for (int bin = 0; bin < kBins; ++bin) {
-    const size_t at = (((size_t)(k & 1) * kBins + bin) * kQueues + lane) * kQueueStride;
-    const unsigned long long qc = A.evq_count[at];
-    Q[bin].q_incl = wave_scan_add((int)(qc & 0xffffffffull));
-    Q[bin].n_queued = __builtin_amdgcn_readlane(Q[bin].q_incl, kWave - 1);
-    const int n_listed = __builtin_amdgcn_readlane(wave_scan_add((int)(qc >> 32)), kWave - 1);
-    // one group of K queued tiles per event block, K chosen so that a group
-    // lists about 64 tets, at most ev_group_max tiles (a launch-shape
-    // setting: longer groups can make the event blocks the last to finish)
-    int K = n_listed > 0 ? (int)((64ll * Q[bin].n_queued) / n_listed) : 1;
-    K = K < 1 ? 1 : (K > K_max ? K_max : K);
-    Q[bin].K = K;
-    Q[bin].n_groups = (Q[bin].n_queued + K - 1) / K;
-    n_groups += Q[bin].n_groups;
-    if (blockIdx.x == 0)  // the next window's queue starts empty
-      A.evq_count[(((size_t)((k + 1) & 1) * kBins + bin) * kQueues + lane) * kQueueStride] = 0;
-  }
-  if (blockIdx.x == 0 && lane < 8 * kClaimSubs)  // and so do its tile claim counters
-    A.tile_ctr[((size_t)((k + 1) & 1) * 8 * kClaimSubs + (size_t)lane) * kCtrStride] = 0;
-  // event blocks: one per group, a multiple of the 8 XCDs (so that the
-  // diffusion blocks keep their XCD mapping), at most half the grid
-  int E = 0;
-  if (n_groups > 0) {
-    const int cap = G / 2 >= 8 ? (G / 2) & ~7 : (G / 2 > 0 ? G / 2 : 1);
-    E = (n_groups + 7) & ~7;
-    if (E > cap) E = cap;
-  }
-  // with tiles claimed at run time an event block done with its groups
-  // takes diffusion tiles of its XCD (E is a multiple of 8, so block b is on
-  // the XCD of diffusion block b - E)
-  const int GD = G - E;
-  const bool join = A.tile_claim != 0 && GD >= 8 && *as_const(A.n_tiles) >= 8;
-  const bool ev = (int)blockIdx.x < E;
-  if (ev) {
-    event_part<SMAX, RMAX>(A, k, blockIdx.x, E, Q, lds.e);
-    if (!join) return;
-    wave_sync();  // the event layout's last reads are done before the diffusion layout is written
-  }
-  diffusion_part<SMAX, RMAX>(A, k, ev ? (int)(blockIdx.x & 7u) : (int)blockIdx.x - E, GD, lds.d, ev);
-}
-
-__global__ void advance_base_kernel(int32_t* base, int32_t add) { *base += add; }
 
 // Batched reset: one block per chunk.
 __global__ void __launch_bounds__(kBlock) reset_chunks_kernel(const ResetChunk* chunks) {
@@ -1573,7 +1267,7 @@ __global__ void __launch_bounds__(kBlock) reset_chunks_kernel(const ResetChunk* 
     if (threadIdx.x == 0) *c.err = 0;
   }
 }
-__global__ void set_base_kernel(int32_t* base, int32_t value) { *base = value; }
+__global__ void set_step_kernel(int32_t* word, int32_t value) { *word = value; }
 
 // ----------------------------------------------------------- self-tests ----
 // One vector per wave (block j of 64 lanes), so that its key is wave-uniform
@@ -1615,73 +1309,53 @@ inline unsigned grid_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBloc
 
 }  // namespace
 
-// Blocks of a window kernel the device holds at once (occupancy x CUs).
-template <typename K>
-int resident_blocks_of(K kernel) {
-  int dev = 0, n_cu = 0, per_cu = 0;
-  (void)hipGetDevice(&dev);
-  (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-  (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel), kWave, 0);
-  return n_cu > 0 && per_cu > 0 ? n_cu * per_cu : 2048;
+// Blocks of a window kernel the device holds at once (occupancy x CUs), by the
+// model's species count.
+template <int SMAX, int RMAX>
+int window_resident(int S) {
+  static const std::array<int, SMAX + 1> r = [] {
+    std::array<int, SMAX + 1> n{};
+    int dev = 0, n_cu = 0;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+    for (int s = 0; s <= SMAX; ++s) {
+      int per_cu = 0;
+      (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(
+          &per_cu, reinterpret_cast<const void*>(&window_main_kernel<SMAX, RMAX>), kWave, tile_row_bytes<SMAX, RMAX>(s));
+      n[s] = n_cu > 0 && per_cu > 0 ? n_cu * per_cu : 2048;
+    }
+    return n;
+  }();
+  return r[S];
 }
 
 template <int SMAX, int RMAX>
-int main_resident() {
-  static const int r = resident_blocks_of(&window_main_kernel<SMAX, RMAX>);
-  return r;
-}
-
-template <int SMAX, int RMAX>
-int detect_resident() {
-  static const int r = resident_blocks_of(&window_detect_kernel<SMAX, RMAX>);
-  return r;
-}
-
-template <int SMAX, int RMAX>
-hipError_t launch_pair(const StepArgs& a, hipStream_t stream, hipEvent_t* marks) {
+hipError_t launch_one(const StepArgs& a, hipStream_t stream, hipEvent_t* marks) {
   if (marks) (void)hipEventRecord(marks[0], stream);
-  hipLaunchKernelGGL((window_detect_kernel<SMAX, RMAX>), dim3((unsigned)a.detect_grid), dim3(kWave), 0,
-                     stream, a);
+  hipLaunchKernelGGL((window_main_kernel<SMAX, RMAX>), dim3((unsigned)a.grid), dim3(kWave),
+                     (tile_row_bytes<SMAX, RMAX>(a.S)), stream, a);
   if (marks) (void)hipEventRecord(marks[1], stream);
-  hipLaunchKernelGGL((window_main_kernel<SMAX, RMAX>), dim3((unsigned)a.main_grid), dim3(kWave), 0, stream, a);
-  if (marks) (void)hipEventRecord(marks[2], stream);
   return hipGetLastError();
 }
 
-void grid_resident(int S, int R, int* detect, int* main) {
-  if (S <= 4 && R <= 4) {
-    *detect = detect_resident<4, 4>();
-    *main = main_resident<4, 4>();
-  } else if (S <= 8 && R <= 8) {
-    *detect = detect_resident<8, 8>();
-    *main = main_resident<8, 8>();
-  } else if (S <= 12 && R <= 12) {
-    *detect = detect_resident<12, 12>();
-    *main = main_resident<12, 12>();
-  } else if (S <= 16 && R <= 24) {
-    *detect = detect_resident<16, 24>();
-    *main = main_resident<16, 24>();
-  } else {
-    *detect = detect_resident<16, 32>();
-    *main = main_resident<16, 32>();
-  }
+int grid_resident(int S, int R) {
+  if (S <= 4 && R <= 4) return window_resident<4, 4>(S);
+  if (S <= 8 && R <= 8) return window_resident<8, 8>(S);
+  if (S <= 12 && R <= 12) return window_resident<12, 12>(S);
+  if (S <= 16 && R <= 24) return window_resident<16, 24>(S);
+  return window_resident<16, 32>(S);
 }
 
 hipError_t launch_window(const StepArgs& a, hipStream_t stream, hipEvent_t* marks) {
-  if (a.S <= 4 && a.R <= 4) return launch_pair<4, 4>(a, stream, marks);
-  if (a.S <= 8 && a.R <= 8) return launch_pair<8, 8>(a, stream, marks);
-  if (a.S <= 12 && a.R <= 12) return launch_pair<12, 12>(a, stream, marks);
-  if (a.S <= 16 && a.R <= 24) return launch_pair<16, 24>(a, stream, marks);
-  return launch_pair<16, 32>(a, stream, marks);
+  if (a.S <= 4 && a.R <= 4) return launch_one<4, 4>(a, stream, marks);
+  if (a.S <= 8 && a.R <= 8) return launch_one<8, 8>(a, stream, marks);
+  if (a.S <= 12 && a.R <= 12) return launch_one<12, 12>(a, stream, marks);
+  if (a.S <= 16 && a.R <= 24) return launch_one<16, 24>(a, stream, marks);
+  return launch_one<16, 32>(a, stream, marks);
 }
 
-hipError_t launch_advance_base(int32_t* base, int32_t add, hipStream_t stream) {
-  hipLaunchKernelGGL(advance_base_kernel, dim3(1), dim3(1), 0, stream, base, add);
-  return hipGetLastError();
-}
-
-hipError_t launch_set_base(int32_t* base, int32_t value, hipStream_t stream) {
-  hipLaunchKernelGGL(set_base_kernel, dim3(1), dim3(1), 0, stream, base, value);
+hipError_t launch_set_step(int32_t* words, int32_t step, hipStream_t stream) {
+  hipLaunchKernelGGL(set_step_kernel, dim3(1), dim3(1), 0, stream, words + (step & 1), step);
   return hipGetLastError();
 }
 

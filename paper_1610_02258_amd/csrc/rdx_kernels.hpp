@@ -52,47 +52,32 @@ struct alignas(16) RunDesc {
   int32_t n_full;              // steps < n_full last tau, step n_full (if < n_steps) tau_last
   uint32_t window0;            // run-local window index of step 0
   uint32_t key0, key1;         // Philox key = seed
+  uint32_t dmask;              // species with D > 0
+  uint32_t pad;
   double tau, tau_last;
   double D[16];                // diffusion coefficients
 };
 
 // Arguments of one window of a batch (identical for every window of a
-// sequence except k_rel).
+// sequence except step and parity).
 struct StepArgs {
   const RunDesc* runs;
   const int2* tile_map;        // [n_tiles] (run, first tet of the tile within the run)
   const int32_t* n_tiles;      // device: number of tiles
-  const int32_t* step_base;    // device: step index of k_rel = 0 (nullptr: 0)
-  int32_t k_rel;
+  int32_t* step_words;         // device: the step index of the next window of parity p in word p (the
+                               // window of step k writes word (k + 1) & 1)
+  int32_t step;                // step index, or -1: read it from step_words[parity] (captured graphs)
+  int32_t parity;              // step & 1
   int32_t S, R;
-  int32_t detect_grid;         // persistent grid of the detect kernel
-  int32_t main_grid;           // grid of the main kernel (event blocks + persistent diffusion blocks), >= 2
-  int32_t ev_group_max;        // most queued tiles an event block takes as one group (1..64)
-  double heavy_events;         // a listed tet with a0 tau_k above this goes to the heavy bin
+  int32_t grid;                // persistent blocks
   int32_t single_run;          // 1: one run, tile t is (run 0, first tet 64 t) without the tile map
   const DevModel* model;
   int32_t info[32];            // = model->info, in kernel arguments for scalar loads
   int32_t n_pairs;             // distinct reactant pairs of the second-order reactions
   int32_t pairs[32];           // a | b << 8 | (a == b) << 16
-  // worklist of the tets whose first SSA event falls inside the window: the
-  // entries of tile t are slots 64 t .. 64 t + wl_tile_count[t] - 1
-  unsigned long long* wl_mask; // [tiles] listed tets of each tile (bit = lane)
-  int32_t* wl_tile_count;      // [tiles], valid for the tiles in the queue
-  // queues of the tiles with listed tets, one per bin (heavy: tets expected
-  // to have more than heavy_events events; light: the others), each in
-  // kQueues sub-queues (tile t goes to sub-queue t mod kQueues, slots
-  // q * evq_cap ...) so that no counter is contended by every tile; a tile's
-  // listed tets take its worklist slots heavy first, wl_tile_count[t] =
-  // heavy | light << 8
-  int32_t* evq;                // [kBins][kQueues][evq_cap]
-  int32_t evq_cap;
-  unsigned long long* evq_count;  // [2][kBins][kQueues][16] by step parity, one 128-byte line per
-                                  // counter: queued tiles (low word), their listed tets (high word)
-  int32_t* wl_tet;
-  // diffusion tiles claimed at run time: after its first (static) tile, a
-  // diffusion block takes the next unclaimed tile of its sub-range of its
-  // XCD's range from tile_ctr[(k & 1)][xcd][sub] (one 128-byte line each);
-  // 0: static ranges
+  // tiles claimed at run time: after its first (static) tile, a block takes
+  // the next unclaimed tile of its sub-range of its XCD's range from
+  // tile_ctr[(k & 1)][xcd][sub] (one 128-byte line each); 0: static ranges
   int32_t tile_claim;
   int32_t* tile_ctr;           // [2][8][kClaimSubs][kCtrStride] by step parity
 };
@@ -100,30 +85,22 @@ struct StepArgs {
 constexpr int kCtrStride = 32;  // int32 per claim counter line
 constexpr int kClaimSubs = 8;   // claim counters (sub-ranges) per XCD range
 
-constexpr int kQueues = 64;
-constexpr int kBins = 2;  // heavy, light
-constexpr int kQueueStride = 16;  // u64 per counter line
-
 // Tallies are spread over this many slots per run (block b adds to slot
 // b mod kTallySlots), so that blocks finishing together do not queue on one
 // address.
 constexpr int kTallySlots = 64;
 constexpr int kTallyWords = 4;  // SSA events, molecules moved, face moves, unused
 
-// Blocks of the detect and of the main kernel for (S, R) the device holds at
-// once (occupancy x compute units).
-void grid_resident(int S, int R, int* detect, int* main);
+// Blocks of the window kernel for (S, R) the device holds at once (occupancy x
+// compute units).
+int grid_resident(int S, int R);
 
-// One window: the detect kernel, then the main kernel; the instance is picked
-// by (S, R).  Both are enqueued on `stream`; when `marks` is given,
-// marks[0..2] are recorded before, between and after.
+// One window; the instance is picked by (S, R).  Enqueued on `stream`; when
+// `marks` is given, marks[0..1] are recorded before and after.
 hipError_t launch_window(const StepArgs& a, hipStream_t stream, hipEvent_t* marks = nullptr);
 
-// *base += add (one thread): advances the step base at the end of a replayed
-// sequence of windows.
-hipError_t launch_advance_base(int32_t* base, int32_t add, hipStream_t stream);
-// *base = value (one thread).
-hipError_t launch_set_base(int32_t* base, int32_t value, hipStream_t stream);
+// step_words[step & 1] = step (one thread).
+hipError_t launch_set_step(int32_t* step_words, int32_t step, hipStream_t stream);
 
 // One chunk of a batched reset: elements [begin, end) of a run's counts are
 // copied from src to dst and cleared in other; the chunk with begin == 0 also

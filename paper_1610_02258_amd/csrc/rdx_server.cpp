@@ -341,14 +341,14 @@ rdx_status rdx_server_create(const rdx_model* structure, const rdx_server_option
   std::unique_ptr<rdx_server> s(new (std::nothrow) rdx_server());
   if (!s) return set_error(RDX_ENOMEM, "host allocation failed");
   (void)hipGetDevice(&s->device);
-  // default: at most 1024 resident requests, and their padded worklist tiles
+  // default: at most 1024 resident requests, and the tiles their last tets pad
   // at most an eighth of the budget
   const size_t wl_tet0 = Engine::worklist_bytes_per_tet(proto.S);
   const int max_runs = opts->max_runs
                            ? opts->max_runs
                            : (int)std::max<size_t>(1, std::min<size_t>(1024, opts->hbm_budget_bytes / (512 * wl_tet0)));
   s->tick_windows = opts->tick_windows ? opts->tick_windows : 8;
-  // the budget holds the worklist (per tet of capacity, plus a padded tile
+  // the budget holds the tile map (per tet of capacity, plus a padded tile
   // per resident run) and the runs' state
   const size_t wl_tet = Engine::worklist_bytes_per_tet(proto.S);
   const size_t pad = 64 * (size_t)max_runs * wl_tet;
