@@ -556,9 +556,7 @@ __device__ __forceinline__ int32_t* run_counts(cptr<RunDesc> rd, uint32_t window
 // Everything one lane reads from global memory for its tet.
 template <int SMAX>
 struct TetData {
-  // counts as one vector value, so that a uniform (run-time) species index
-  // selects a register rather than spilling the array to memory
-  int __attribute__((ext_vector_type(SMAX))) N;
+  int N[SMAX];
   double nav;
   int reg;
 };
@@ -613,6 +611,13 @@ __device__ __forceinline__ void settle(TetData<SMAX>& d) {
   asm volatile("" : "+v"(d.nav), "+v"(d.reg));
 }
 
+// tau_k D_s of the run.
+template <int SMAX>
+__device__ __forceinline__ void set_run(double (&tauD)[SMAX], cptr<RunDesc> rd, double d, int k, int S, int lane) {
+  asm volatile("" : "+v"(d));  // waited for on every path
+  if (lane < SMAX) tauD[lane] = run_tau(rd, k) * (lane < S ? d : 0.0);
+}
+
 __device__ __forceinline__ unsigned long long* tally_slot(cptr<RunDesc> rd) {
   return rd->tally + kTallyWords * (blockIdx.x & (kTallySlots - 1));
 }
@@ -658,12 +663,8 @@ constexpr int ssa_lanes() {
 // for an absent one, A + A.
 struct LaneReaction {
   uint32_t info;  // s0 | s1 << 8 | order << 16, 0xff000000 if there is none
-  __device__ __forceinline__ void load(const StepArgs& A, int r) {
-    info = 0xff000000u;
-    if (r < A.R) {
-      const uint32_t i = (uint32_t)as_const(reinterpret_cast<const int*>(A.model))[offsetof(DevModel, info) / 4 + r];
-      info = ((i >> 8) & 0xffffu) | ((i & 0xffu) << 16);
-    }
+  __device__ __forceinline__ void set(uint32_t i, bool any) {
+    info = any ? ((i >> 8) & 0xffffu) | ((i & 0xffu) << 16) : 0xff000000u;
   }
 };
 
@@ -762,14 +763,17 @@ __device__ __forceinline__ double lane_read(double v, int from) {
 template <int SMAX, int RMAX>
 __device__ __forceinline__ unsigned int ssa_window(TileLds<SMAX, RMAX>& L, double* rows, bool run, uint32_t key0, uint32_t key1,
                                                    uint32_t window, uint32_t tet, double tau, double nav, const double (&kc)[2],
-                                                   const LaneReaction (&lr)[2], int& N, double& O, double& t,
+                                                   const LaneReaction (&lr_in)[2], int& N, double& O, double& t,
                                                    bool& touched, int& err) {
   constexpr int GL = ssa_lanes<SMAX, RMAX>();
   constexpr int RPL = (RMAX + GL - 1) / GL;  // reactions of a lane
   static_assert(RPL <= 2 && GL >= SMAX && GL <= 16, "a lane per species, at most two reactions a lane");
-  const int lane = threadIdx.x;
+  int lane = threadIdx.x;
+  renew(lane);  // (what follows from it is not kept over the tile)
   const int j = lane & (GL - 1), g0 = lane - j;
   constexpr uint32_t group = (1u << GL) - 1u;
+  LaneReaction lr[2] = {lr_in[0], lr_in[1]};
+  asm volatile("" : "+v"(lr[0].info), "+v"(lr[1].info));
   double* const a = rows + (size_t)(g0 / GL) * RMAX;
   unsigned int events = 0;
   if (run) {
@@ -882,8 +886,15 @@ window_main_kernel(const StepArgs A) {
   __shared__ TileLds<SMAX, RMAX> L;
   int* const acc = reinterpret_cast<int*>(tile_rows);
   uint32_t* const items = tile_rows + A.S * kWave;
-  const int k = A.step >= 0 ? A.step : as_const(A.step_words)[A.parity];
+  // The first tile's counts are at the end of a chain of loads (arguments,
+  // step and run, rows) that a block of two or three tiles feels: what of it
+  // is known by now is read at once, a word of each cache line, so that later
+  // reads find it in the scalar cache.
+  const int step_word = as_const(A.step_words)[A.parity];
   const int n_tiles = *as_const(A.n_tiles);
+  asm volatile("" ::"s"(step_word), "s"(n_tiles), "s"(A.S), "s"(A.info[4]), "s"(A.info[20]), "s"(A.n_pairs),
+               "s"(A.pairs[12]), "s"(A.tile_claim));
+  const int k = A.step >= 0 ? A.step : step_word;
   const int b = blockIdx.x, G = gridDim.x;
   if (b == 0) {
     // the next window's step index and claim counters (nothing in this window
@@ -903,38 +914,65 @@ window_main_kernel(const StepArgs A) {
   // so every block ends, and the slowest finishes within about one tile of
   // the others.
   const bool claim = A.tile_claim != 0 && G >= 8 && n_tiles >= 8;
-  const int dyn0 = tr.first - (b >> 3) + tr.stride;  // lo + Gx
-  const int nsub = tr.stride < kClaimSubs ? (tr.stride > 0 ? tr.stride : 1) : kClaimSubs;
-  const int sub = (b >> 3) % nsub;
-  int32_t* const ctr =
-      A.tile_ctr + ((size_t)(k & 1) * 8 * kClaimSubs + (size_t)(b & 7) * kClaimSubs + (size_t)sub) * kCtrStride;
-  const int n_claim = tr.end > dyn0 ? tr.end - dyn0 : 0;
-  const int sub_lo = dyn0 + (int)(((long long)n_claim * sub) / nsub);
-  const int sub_hi = dyn0 + (int)(((long long)n_claim * (sub + 1)) / nsub);
-  constexpr int GL = ssa_lanes<SMAX, RMAX>();
-  {
-    const cptr<uint32_t> mw = as_const(reinterpret_cast<const uint32_t*>(A.model));
-    uint32_t* const dw = reinterpret_cast<uint32_t*>(L.delta);
-#pragma unroll
-    for (int j = 0; j < (RMAX * 4 + kWave - 1) / kWave; ++j) {
-      const int q = kWave * j + (int)threadIdx.x;
-      if (q < RMAX * 4) dw[q] = mw[offsetof(DevModel, delta) / 4 + q];
-    }
+  int sub_lo = 0, sub_hi = 0;
+  int32_t* ctr = A.tile_ctr;
+  if (claim) {
+    const int dyn0 = tr.first - (b >> 3) + tr.stride;  // lo + Gx
+    const int n_claim = tr.end > dyn0 ? tr.end - dyn0 : 0;  // at most 2^22 (64 tets a tile, an eighth of them)
+    const bool all = tr.stride >= kClaimSubs;
+    const int nsub = all ? kClaimSubs : (tr.stride > 0 ? tr.stride : 1);
+    const int sub = all ? (b >> 3) % kClaimSubs : (b >> 3) % nsub;
+    ctr += ((size_t)A.parity * 8 * kClaimSubs + (size_t)(b & 7) * kClaimSubs + (size_t)sub) * kCtrStride;
+    sub_lo = dyn0 + (all ? n_claim * sub / kClaimSubs : n_claim * sub / nsub);
+    sub_hi = dyn0 + (all ? n_claim * (sub + 1) / kClaimSubs : n_claim * (sub + 1) / nsub);
   }
-  LaneReaction lr[2];
-  lr[0].load(A, (int)threadIdx.x & (GL - 1));
-  lr[1].load(A, ((int)threadIdx.x & (GL - 1)) + GL);
+  constexpr int GL = ssa_lanes<SMAX, RMAX>();
   int raw = 0;  // lane 0: the counter value of the claim in flight
-  if (claim && threadIdx.x == 0) raw = atomicAdd(ctr, 1);
+  // (At an address known to be uniform the compiler would add for the wave and
+  // wait for the result at once.)
+  auto claim_next = [&] {
+    int own = 0;
+    renew(own);
+    if (claim && threadIdx.x == 0) raw = atomicAdd(ctr + own, 1);
+  };
+  claim_next();
   cptr<RunDesc> cached = nullptr;  // the run whose tables are in LDS
   unsigned long long n_ev = 0, n_moved = 0;
   uint32_t n_faces = 0;
 
   TileAt here{nullptr, 0}, there{nullptr, 0};  // this tile, the next one
   TetData<SMAX> cur, nxt;
+  double first_d = 0.0;
   if (tr.first < tr.end) {
     here = tile_at(A, tr.first);
+    asm volatile("" ::"s"(here.rd->cnt[0]), "s"(here.rd->n_steps), "s"(here.rd->tau), "s"(here.rd->D[4]),
+                 "s"(here.rd->D[12]));
     load_tet<SMAX>(here, k, A.S, threadIdx.x, cur);
+    first_d = here.rd->D[threadIdx.x & 15];
+  }
+  // the tables, in flight beside the first tile
+  LaneReaction lr[2];
+  {
+    constexpr int kWords = RMAX * 4, kPer = (kWords + kWave - 1) / kWave;
+    const cptr<uint32_t> mw = as_const(reinterpret_cast<const uint32_t*>(A.model));
+    const int t = (int)threadIdx.x, j = t & (GL - 1);
+    uint32_t dw[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) dw[q] = mw[offsetof(DevModel, delta) / 4 + (kWave * q + t) % kWords];
+    const uint32_t i0 = mw[offsetof(DevModel, info) / 4 + j], i1 = mw[offsetof(DevModel, info) / 4 + j + GL];
+    lr[0].set(i0, j < A.R);
+    lr[1].set(i1, j + GL < A.R);
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      if (kWave * q + t < kWords) reinterpret_cast<uint32_t*>(L.delta)[kWave * q + t] = dw[q];
+    }
+  }
+  if (tr.first < tr.end) {
+    if (run_active(here.rd, k)) {
+      cached = here.rd;
+      set_run(L.tauD, here.rd, first_d, k, A.S, threadIdx.x);
+    }
+    settle<SMAX>(cur);
   }
   int claimed = __builtin_amdgcn_readfirstlane(raw);
 
@@ -943,7 +981,7 @@ window_main_kernel(const StepArgs A) {
     asm volatile("" : "+v"(lane), "+s"(S));
     const unsigned long long below = (1ull << lane) - 1ull;
     const cptr<RunDesc> rd = here.rd;
-    const int base = here.base;
+    const int base = __builtin_amdgcn_readfirstlane(here.base);
     const int T = rd->T;
     const bool stepping = run_active(rd, k);  // else the tile only forwards the prefetch
     const uint32_t window = run_window(rd, k);
@@ -961,8 +999,7 @@ window_main_kernel(const StepArgs A) {
         n_ev = n_moved = 0;
         n_faces = 0;
       }
-      const double d = lane < S ? rd->D[lane < SMAX ? lane : 0] : 0.0;
-      if (lane < SMAX) L.tauD[lane] = tau * d;
+      set_run(L.tauD, rd, rd->D[lane & 15], k, S, lane);
       cached = rd;
     }
     TetGeo tg;  // in flight until the listing is done
@@ -970,7 +1007,11 @@ window_main_kernel(const StepArgs A) {
     const uint32_t key0 = rd->key0, key1 = rd->key1, dmask = rd->dmask;
     const double nav = cur.nav;
     const int reg = cur.reg;
-    auto N = cur.N;
+    // the counts as one vector value, so that a uniform (run-time) species
+    // index selects a register rather than spilling the array to memory
+    int __attribute__((ext_vector_type(SMAX))) N;
+#pragma unroll
+    for (int s = 0; s < SMAX; ++s) N[s] = cur.N[s];
     int errbits = 0;
     int most = 0;
 #pragma unroll
@@ -1058,7 +1099,10 @@ window_main_kernel(const StepArgs A) {
         const double nav_t = lane_read(nav, Lt);
         const int reg_t = __builtin_amdgcn_ds_bpermute(4 * Lt, reg);
         const cptr<double> kw = as_const(rd->kcst) + reg_t * 32;
-        const double kc[2] = {j < RMAX ? kw[j] : 0.0, j + GL < RMAX ? kw[j + GL] : 0.0};
+        double kc[2] = {j < RMAX ? kw[j] : 0.0, j + GL < RMAX ? kw[j + GL] : 0.0};
+        // (a load that some path leaves unread has every later write of its
+        // register wait for all memory operations)
+        asm volatile("" : "+v"(kc[0]), "+v"(kc[1]));
         double O = 0.0, t = 0.0;
         bool touched = false;
         int err = 0;
@@ -1104,7 +1148,7 @@ window_main_kernel(const StepArgs A) {
         if (tile < tr.end) {
           there = tile_at(A, tile);
           load_tet<SMAX>(there, k, S, lane, nxt);
-          if (claim && lane == 0) raw = atomicAdd(ctr, 1);  // the tile after next
+          claim_next();  // the tile after next
         }
         __builtin_amdgcn_sched_barrier(0);
         // Items in five classes, each species-major: more than 16 molecules
@@ -1116,6 +1160,7 @@ window_main_kernel(const StepArgs A) {
         // Where no tet has more than four of any species there is one class,
         // listed without the search for it.
         renew<SMAX>(N);
+        renew(lane);
         if (__ballot(most > 4) == 0ull) {
 #pragma unroll
           for (int s = 0; s < SMAX; ++s) {
@@ -1181,7 +1226,10 @@ window_main_kernel(const StepArgs A) {
         }
         const bool plain = valid && at >= n_drawn;
         if (any_wide) {  // a count that does not fit its field is read from the count buffer
-          if (plain && m == 0) m = run_counts(rd, window, 0u)[(size_t)sp * T + base + Ln];
+          if (plain && m == 0) {
+            m = run_counts(rd, window, 0u)[(size_t)sp * T + base + Ln];
+            renew(m);  // the other rounds do not wait for memory
+          }
         }
         if (plain) nb = (double)m;
         general = general || __ballot(m > kSmallM) != 0ull;
