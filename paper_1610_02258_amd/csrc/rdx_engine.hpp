@@ -215,7 +215,7 @@ class Engine {
   // `step0` on
   rdx_status launch_plain(const StepArgs& a, int64_t step0, int64_t K, hipStream_t stream);
   rdx_status launch_graphs(const StepArgs& a, int64_t step0, int64_t reps, hipStream_t stream);
-  int grid_for(int64_t n_tiles, int div, bool claim) const;
+  void cover(int64_t n_tiles, const ExecShape& sh, StepArgs* a) const;
   void free_graphs();
 
   int S_ = 0, R_ = 0;

@@ -25,6 +25,7 @@
 #include <hip/hip_runtime.h>
 
 #include <array>
+#include <atomic>
 #include <cstdint>
 #include <type_traits>
 
@@ -252,8 +253,8 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
 
 // -------------------------------------------------------- window kernel ----
 // A window of a batch is one launch of window_main_kernel: persistent blocks of one
-// wave (64 lanes), one lane per tet, a tile of up to 64 tets at a time (a tile
-// belongs to one run).  Per tile:
+// wave (64 lanes), one lane per tet, a tile of 64, 32 or 16 tets at a time (a
+// tile belongs to one run).  Per tile:
 //
 // Listing: a0 from regrouped coefficients and the tet's first SSA uniform.
 // A tet whose first event may fall inside the window is listed.
@@ -540,9 +541,10 @@ struct TileAt {
 __device__ __forceinline__ TileAt tile_at(const StepArgs& A, int tile) {
   // with one run the tile map is (0, 64 t): no load on the chain to the counts
   const cptr<int> map = as_const(reinterpret_cast<const int*>(A.tile_map));
-  const int run = A.single_run ? 0 : map[2 * tile];
-  const int first = A.single_run ? tile * kWave : map[2 * tile + 1];
-  return TileAt{as_const(A.runs) + run, first};
+  const int cut = 6 - A.tile_shift, t = tile >> cut, part = (tile & ((1 << cut) - 1)) << A.tile_shift;
+  const int run = A.single_run ? 0 : map[2 * t];
+  const int first = A.single_run ? t * kWave : map[2 * t + 1];
+  return TileAt{as_const(A.runs) + run, first + part};
 }
 
 __device__ __forceinline__ bool run_active(cptr<RunDesc> rd, int k) { return k < rd->n_steps; }
@@ -568,10 +570,10 @@ struct TetGeo {
 // Row pointers are uniform (scalar registers) and end at the tile's first tet;
 // the lane's 32-bit offset is the only vector part of an address.
 template <int SMAX>
-__device__ __forceinline__ void load_tet(const TileAt& at, int k, int S, int lane, TetData<SMAX>& d) {
+__device__ __forceinline__ void load_tet(const TileAt& at, int k, int S, int width, int lane, TetData<SMAX>& d) {
   const cptr<RunDesc> rd = at.rd;
   const int T = rd->T;
-  const bool active = run_active(rd, k) && lane < T - at.base;
+  const bool active = run_active(rd, k) && lane < width && lane < T - at.base;
   renew_s(S);
 #pragma unroll
   for (int s = 0; s < SMAX; ++s) d.N[s] = 0;
@@ -680,6 +682,7 @@ struct TileLds {
   double nbar[kDrawn];
   int npost[kDrawn];
   uint16_t drawn[kDrawn];
+  int ctr, sub_lo, sub_hi;  // the block's claim counter (index) and sub-range
   int8_t delta[RMAX][16];  // net changes by reaction and species
   double tauD[SMAX];       // tau_k D_s of the current run
   int4 nbr[kWave];        // neighbours, counted from the tile's first tet
@@ -891,7 +894,8 @@ window_main_kernel(const StepArgs A) {
   // is known by now is read at once, a word of each cache line, so that later
   // reads find it in the scalar cache.
   const int step_word = as_const(A.step_words)[A.parity];
-  const int n_tiles = *as_const(A.n_tiles);
+  const int width = 1 << A.tile_shift;  // tets of a tile
+  const int n_tiles = *as_const(A.n_tiles) << (6 - A.tile_shift);
   asm volatile("" ::"s"(step_word), "s"(n_tiles), "s"(A.S), "s"(A.info[4]), "s"(A.info[20]), "s"(A.n_pairs),
                "s"(A.pairs[12]), "s"(A.tile_claim));
   const int k = A.step >= 0 ? A.step : step_word;
@@ -907,35 +911,33 @@ window_main_kernel(const StepArgs A) {
   // differ in cost): the block's first tile is its static one, lo + j; the
   // tiles from lo + Gx on are cut into kClaimSubs sub-ranges (fewer if the
   // XCD has fewer blocks), each handed out in order by a counter of its own
-  // to the blocks with j mod kClaimSubs equal to its index, each claim
-  // issued a tile ahead so that its latency hides behind a tile's work.
+  // to the blocks with j mod kClaimSubs equal to its index.
   // Eight counters per XCD keep the claims at a window's start from queueing
   // on one address.  A block stops at its first claim past its sub-range,
   // so every block ends, and the slowest finishes within about one tile of
   // the others.
   const bool claim = A.tile_claim != 0 && G >= 8 && n_tiles >= 8;
-  int sub_lo = 0, sub_hi = 0;
-  int32_t* ctr = A.tile_ctr;
   if (claim) {
     const int dyn0 = tr.first - (b >> 3) + tr.stride;  // lo + Gx
     const int n_claim = tr.end > dyn0 ? tr.end - dyn0 : 0;  // at most 2^22 (64 tets a tile, an eighth of them)
     const bool all = tr.stride >= kClaimSubs;
     const int nsub = all ? kClaimSubs : (tr.stride > 0 ? tr.stride : 1);
     const int sub = all ? (b >> 3) % kClaimSubs : (b >> 3) % nsub;
-    ctr += ((size_t)A.parity * 8 * kClaimSubs + (size_t)(b & 7) * kClaimSubs + (size_t)sub) * kCtrStride;
-    sub_lo = dyn0 + (all ? n_claim * sub / kClaimSubs : n_claim * sub / nsub);
-    sub_hi = dyn0 + (all ? n_claim * (sub + 1) / kClaimSubs : n_claim * (sub + 1) / nsub);
+    L.ctr = ((A.parity * 8 + (b & 7)) * kClaimSubs + sub) * kCtrStride;
+    L.sub_lo = dyn0 + (all ? n_claim * sub / kClaimSubs : n_claim * sub / nsub);
+    L.sub_hi = dyn0 + (all ? n_claim * (sub + 1) / kClaimSubs : n_claim * (sub + 1) / nsub);
   }
   constexpr int GL = ssa_lanes<SMAX, RMAX>();
   int raw = 0;  // lane 0: the counter value of the claim in flight
   // (At an address known to be uniform the compiler would add for the wave and
   // wait for the result at once.)
   auto claim_next = [&] {
-    int own = 0;
-    renew(own);
-    if (claim && threadIdx.x == 0) raw = atomicAdd(ctr + own, 1);
+    if (claim && threadIdx.x == 0) {
+      int at = L.ctr;
+      renew(at);
+      raw = atomicAdd(A.tile_ctr + at, 1);
+    }
   };
-  claim_next();
   cptr<RunDesc> cached = nullptr;  // the run whose tables are in LDS
   unsigned long long n_ev = 0, n_moved = 0;
   uint32_t n_faces = 0;
@@ -947,7 +949,7 @@ window_main_kernel(const StepArgs A) {
     here = tile_at(A, tr.first);
     asm volatile("" ::"s"(here.rd->cnt[0]), "s"(here.rd->n_steps), "s"(here.rd->tau), "s"(here.rd->D[4]),
                  "s"(here.rd->D[12]));
-    load_tet<SMAX>(here, k, A.S, threadIdx.x, cur);
+    load_tet<SMAX>(here, k, A.S, width, threadIdx.x, cur);
     first_d = here.rd->D[threadIdx.x & 15];
   }
   // the tables, in flight beside the first tile
@@ -974,8 +976,6 @@ window_main_kernel(const StepArgs A) {
     }
     settle<SMAX>(cur);
   }
-  int claimed = __builtin_amdgcn_readfirstlane(raw);
-
   for (int tile = tr.first; tile < tr.end;) {
     int lane = threadIdx.x, S = A.S;
     asm volatile("" : "+v"(lane), "+s"(S));
@@ -987,7 +987,7 @@ window_main_kernel(const StepArgs A) {
     const uint32_t window = run_window(rd, k);
     const double tau = run_tau(rd, k);
     const int i = base + lane;
-    const bool active = stepping && i < T;
+    const bool active = stepping && lane < width && i < T;
     if (stepping && rd != cached) {
       if (cached != nullptr) {  // tallies are kept per run
         const unsigned long long ev = wave_sum(n_ev), mv = wave_sum(n_moved), fm = wave_sum(n_faces);
@@ -1028,8 +1028,8 @@ window_main_kernel(const StepArgs A) {
     // listed tet without an event is harmless: its SSA ends at the first draw
     // and its items are those of an unlisted tet.
     bool event = false;
+    double a0 = 0.0;
     if (active) {
-      double a0 = 0.0;
       if (rd->region == nullptr) {
         a0 = listing_rate<SMAX>(A, as_const(rd->lcoef), N, nav);
       } else {
@@ -1042,6 +1042,15 @@ window_main_kernel(const StepArgs A) {
           left &= ~__ballot(reg == q);
         }
       }
+    }
+    // The claim of the next tile, its latency behind the rest of the listing.
+    // Where many tets will have events it waits until their SSA is done: a
+    // tile claimed and held meanwhile is the branch's next crowded one, which
+    // then runs after this one instead of beside it (branch 281 us a window
+    // with claims a tile ahead, 225 so; dendrite 241 and 233).
+    const bool early = (int)__popcll(__ballot(tau * a0 > 0.5)) <= 2 * (kWave / GL);
+    if (early) claim_next();
+    {
       if (a0 > 0.0) {
         uint32_t w0 = 0u, w1 = 0u, w2 = (uint32_t)i, w3 = window;
         philox4x32_10(w0, w1, w2, w3, key0, key1);
@@ -1143,12 +1152,16 @@ window_main_kernel(const StepArgs A) {
       if (last) {
         // the next tile's loads are in flight while the items are listed
         __builtin_amdgcn_sched_barrier(0);
-        if (claim) tile = sub_lo + claimed < sub_hi ? sub_lo + claimed : tr.end;
-        else tile += tr.stride;
+        if (claim) {
+          if (!early) claim_next();
+          tile = __builtin_amdgcn_readfirstlane(L.sub_lo) + __builtin_amdgcn_readfirstlane(raw);
+          if (tile >= __builtin_amdgcn_readfirstlane(L.sub_hi)) tile = tr.end;
+        } else {
+          tile += tr.stride;
+        }
         if (tile < tr.end) {
           there = tile_at(A, tile);
-          load_tet<SMAX>(there, k, S, lane, nxt);
-          claim_next();  // the tile after next
+          load_tet<SMAX>(there, k, S, width, lane, nxt);
         }
         __builtin_amdgcn_sched_barrier(0);
         // Items in five classes, each species-major: more than 16 molecules
@@ -1161,10 +1174,12 @@ window_main_kernel(const StepArgs A) {
         // listed without the search for it.
         renew<SMAX>(N);
         renew(lane);
+        int mobile = (int)dmask;
+        renew_s(mobile);
         if (__ballot(most > 4) == 0ull) {
 #pragma unroll
           for (int s = 0; s < SMAX; ++s) {
-            const bool has = N[s] > 0 && ((dmask >> s) & 1u);
+            const bool has = N[s] > 0 && ((mobile >> s) & 1);
             const unsigned long long bs = __ballot(has);
             if (has) items[n_item + (int)__popcll(bs & below)] = (uint32_t)(N[s] << 10) | (uint32_t)(lane << 4) | (uint32_t)s;
             n_item += (int)__popcll(bs);
@@ -1183,7 +1198,7 @@ window_main_kernel(const StepArgs A) {
             const uint32_t span = cls == 0 ? 0x7fffffffu - (kSmallM + 1) : 3u;
             uint32_t todo =
                 cls == 0 ? sets[0] : (cls == 1 ? sets[1] : (cls == 2 ? sets[2] : (cls == 3 ? sets[3] : sets[4])));
-            todo &= dmask;
+            todo &= (uint32_t)mobile;
 #pragma unroll 1
             for (; todo != 0u; todo &= todo - 1u) {
               const int s = __builtin_ctz(todo);
@@ -1198,7 +1213,6 @@ window_main_kernel(const StepArgs A) {
           }
         }
         settle<SMAX>(nxt);
-        claimed = __builtin_amdgcn_readfirstlane(raw);
       }
       wave_sync();
       const int total = n_drawn + n_item;
@@ -1254,7 +1268,7 @@ window_main_kernel(const StepArgs A) {
           if (m != n) atomicAdd(own + Ln, m - n);
 #define RDX_DEPOSIT(t, v)                                              \
           if (v) {                                                     \
-            if ((unsigned)(t) < (unsigned)kWave) atomicAdd(own + (t), (v)); \
+            if ((unsigned)(t) < (unsigned)width) atomicAdd(own + (t), (v)); \
             else atomicAdd(row + (t), (v));                            \
             ++n_faces;                                                 \
           }
@@ -1361,20 +1375,18 @@ inline unsigned grid_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBloc
 // model's species count.
 template <int SMAX, int RMAX>
 int window_resident(int S) {
-  static const std::array<int, SMAX + 1> r = [] {
-    std::array<int, SMAX + 1> n{};
-    int dev = 0, n_cu = 0;
+  static std::array<std::atomic<int>, SMAX + 1> known{};  // 0: not asked yet
+  int n = known[S].load(std::memory_order_relaxed);
+  if (n == 0) {
+    int dev = 0, n_cu = 0, per_cu = 0;
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
-    for (int s = 0; s <= SMAX; ++s) {
-      int per_cu = 0;
-      (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &per_cu, reinterpret_cast<const void*>(&window_main_kernel<SMAX, RMAX>), kWave, tile_row_bytes<SMAX, RMAX>(s));
-      n[s] = n_cu > 0 && per_cu > 0 ? n_cu * per_cu : 2048;
-    }
-    return n;
-  }();
-  return r[S];
+    (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &per_cu, reinterpret_cast<const void*>(&window_main_kernel<SMAX, RMAX>), kWave, tile_row_bytes<SMAX, RMAX>(S));
+    n = n_cu > 0 && per_cu > 0 ? n_cu * per_cu : 2048;
+    known[S].store(n, std::memory_order_relaxed);
+  }
+  return n;
 }
 
 template <int SMAX, int RMAX>

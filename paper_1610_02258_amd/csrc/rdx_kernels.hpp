@@ -70,6 +70,7 @@ struct StepArgs {
   int32_t parity;              // step & 1
   int32_t S, R;
   int32_t grid;                // persistent blocks
+  int32_t tile_shift;          // a block's tile: 1 << tile_shift tets, an entry of the tile map cut in equal parts
   int32_t single_run;          // 1: one run, tile t is (run 0, first tet 64 t) without the tile map
   const DevModel* model;
   int32_t info[32];            // = model->info, in kernel arguments for scalar loads

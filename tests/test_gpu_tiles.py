@@ -65,3 +65,29 @@ def test_tiles_match_oracle(oracle_lib, S, R, box, mean):
         assert (st.ssa_events, st.moves, st.face_moves) == (ref.tallies.ssa_events, ref.tallies.moves,
                                                             ref.tallies.face_moves)
         sim.close()
+
+
+@pytest.mark.parametrize("claim", [0, 1])
+@pytest.mark.parametrize("box", [(15, 15, 15), (20, 20, 15)])
+def test_tile_widths_match_oracle(oracle_lib, box, claim):
+    """Runs of 317 and 563 tiles on a quarter of the resident blocks, where
+    tiles of 32 and of 64 tets are taken (the small runs above take 16)."""
+    from paper_1610_02258_amd import rdx
+    rng = np.random.default_rng(sum(box))
+    mesh = _mesh(*box, 2, seed=3)
+    T = len(mesh["tets"])
+    md = random_model(rng, 3, 5, 2)
+    md["kcst"] *= 3e-4 / oracle_lib.Instance(mesh, md, 5).tau
+    md["kcst"][:, md["lhs"].sum(1) == 0] *= 0.01
+    counts = random_counts(rng, 3, T, 3.0)
+    print(f"case: T={T} tile_claim {claim}", flush=True)
+    ref = oracle_lib.Instance(mesh, md, 5)
+    sim = rdx.Sim(mesh, md, 5)
+    sim.set_exec_options(fast_grid_div=4, graph_windows=2, tile_claim=claim)
+    ref.reset(counts)
+    sim.set_counts(counts)
+    for k in (1, 4):
+        ref.step(k)
+        sim.step(k)
+        np.testing.assert_array_equal(sim.get_counts(), ref.counts)
+    sim.close()
