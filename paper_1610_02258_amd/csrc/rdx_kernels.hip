@@ -251,6 +251,19 @@ __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) {
   return v;
 }
 
+// The sum of v over the lanes up to the own one.
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
+#define RDX_STEP(ctrl, rows) v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, rows, 0xf, false)
+  RDX_STEP(0x111, 0xf);  // row_shr:1
+  RDX_STEP(0x112, 0xf);  // row_shr:2
+  RDX_STEP(0x114, 0xf);  // row_shr:4
+  RDX_STEP(0x118, 0xf);  // row_shr:8
+  RDX_STEP(0x142, 0xa);  // row_bcast:15
+  RDX_STEP(0x143, 0xc);  // row_bcast:31
+#undef RDX_STEP
+  return v;
+}
+
 // -------------------------------------------------------- window kernel ----
 // A window of a batch is one launch of window_main_kernel: persistent blocks of one
 // wave (64 lanes), one lane per tet, a tile of 64, 32 or 16 tets at a time (a
@@ -365,7 +378,6 @@ __device__ __forceinline__ void renew_s(uint32_t& a, uint32_t& b) { asm volatile
 // walk; such an item -- only a species changed in the window can have one --
 // is walked word by word in stream order.)
 constexpr int kSmallM = 16;
-constexpr int kPackedCount = 1 << 22;  // counts from here on do not fit an item's packed field
 
 // Leavers by face.
 struct Faces {
@@ -693,9 +705,13 @@ struct TileLds {
 // the next counts of the tile's own tets, [S][64], and a space that holds first,
 // while listed tets run, a row of propensities per tet (and before them the
 // counts on the way to their lanes), then the items, count << 10 | lane << 4 |
-// species, [S * 64] at most.  Sized by S and not by SMAX, ten species take
-// 9.6 KB, and 16 blocks instead of 14 fit a CU.
+// species, [S * 64] at most.  By S and not SMAX, for the blocks a CU holds.
 extern __shared__ __attribute__((aligned(16))) uint32_t tile_rows[];
+// Two bytes an item for up to 12 species, so that 16 blocks fit a CU (the
+// counts that do not fit the word's six bits are read again); four above,
+// where registers hold a CU to 12 blocks.
+template <int SMAX>
+using ItemWord = std::conditional_t<(SMAX <= 12), uint16_t, uint32_t>;
 
 template <int SMAX, int RMAX>
 constexpr int ssa_row_bytes() {
@@ -705,7 +721,7 @@ template <int SMAX, int RMAX>
 constexpr int tile_row_bytes(int S) {
   constexpr int least = ssa_row_bytes<SMAX, RMAX>() > kWave * (int)sizeof(int) ? ssa_row_bytes<SMAX, RMAX>()
                                                                                : kWave * (int)sizeof(int);
-  const int items = S * kWave * (int)sizeof(uint32_t);
+  const int items = S * kWave * (int)sizeof(ItemWord<SMAX>);
   return S * kWave * (int)sizeof(int) + (items > least ? items : least);
 }
 
@@ -881,14 +897,18 @@ __device__ __forceinline__ unsigned int ssa_window(TileLds<SMAX, RMAX>& L, doubl
 // Four waves per SIMD for up to 12 species, three above: the tiles are chains
 // of a lone wave and need the others to fill its gaps.  At three, 480,000 tets
 // of 10 species are 3 rounds of tiles and 46.1 us a window, at four 2 rounds
-// and 36.7 us (20 bytes of scratch a lane, outside the loops over items).
-// The larger tables would spill inside them at four.
+// and 36.7 us.  For 16 species four waves take 48 bytes of scratch a lane and
+// items of two bytes, and gain nothing: a million tets of the calcium model
+// 224 us a window, and at three 223.
 template <int SMAX, int RMAX>
 __global__ void __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(SMAX <= 12 ? 4 : 3)))
 window_main_kernel(const StepArgs A) {
   __shared__ TileLds<SMAX, RMAX> L;
   int* const acc = reinterpret_cast<int*>(tile_rows);
-  uint32_t* const items = tile_rows + A.S * kWave;
+  typedef ItemWord<SMAX> item_t;
+  constexpr int kPackedCount = 1 << (8 * (int)sizeof(item_t) - 10);  // counts from here on do not fit an item
+  item_t* const items = reinterpret_cast<item_t*>(tile_rows + A.S * kWave);
+  int* const moved_n = reinterpret_cast<int*>(items);
   // The first tile's counts are at the end of a chain of loads (arguments,
   // step and run, rows) that a block of two or three tiles feels: what of it
   // is known by now is read at once, a word of each cache line, so that later
@@ -1007,9 +1027,7 @@ window_main_kernel(const StepArgs A) {
     const uint32_t key0 = rd->key0, key1 = rd->key1, dmask = rd->dmask;
     const double nav = cur.nav;
     const int reg = cur.reg;
-    // the counts as one vector value, so that a uniform (run-time) species
-    // index selects a register rather than spilling the array to memory
-    int __attribute__((ext_vector_type(SMAX))) N;
+    int N[SMAX];
 #pragma unroll
     for (int s = 0; s < SMAX; ++s) N[s] = cur.N[s];
     int errbits = 0;
@@ -1030,14 +1048,19 @@ window_main_kernel(const StepArgs A) {
     bool event = false;
     double a0 = 0.0;
     if (active) {
+      // the counts as one vector value, so that a uniform (run-time) species
+      // index selects a register rather than spilling the array to memory
+      int __attribute__((ext_vector_type(SMAX))) NV;
+#pragma unroll
+      for (int s = 0; s < SMAX; ++s) NV[s] = N[s];
       if (rd->region == nullptr) {
-        a0 = listing_rate<SMAX>(A, as_const(rd->lcoef), N, nav);
+        a0 = listing_rate<SMAX>(A, as_const(rd->lcoef), NV, nav);
       } else {
         // one region of the tile at a time (neighbouring tets mostly share one)
         unsigned long long left = __ballot(true);
         while (left != 0ull) {
           const int q = __builtin_amdgcn_readlane(reg, __builtin_ctzll(left));
-          const double r = listing_rate<SMAX>(A, as_const(rd->lcoef) + q * kLStride, N, nav);
+          const double r = listing_rate<SMAX>(A, as_const(rd->lcoef) + q * kLStride, NV, nav);
           if (reg == q) a0 = r;
           left &= ~__ballot(reg == q);
         }
@@ -1087,7 +1110,20 @@ window_main_kernel(const StepArgs A) {
     // items of the species their events changed wait for the tile's others,
     // unless they are too many.
     int c0 = 0, n_drawn = 0;
+    uint32_t kept = apart && !event ? 0u : ~0u;  // species whose count is still the tet's item
     for (;;) {
+      if (c0 > 0) {  // after a flush of changed items: the counts again
+        const int32_t* row = run_counts(rd, window, 0u) + base;
+        int n[SMAX];
+#pragma unroll
+        for (int s = 0; s < SMAX; ++s) {
+          n[s] = 0;
+          if (s < S && active) n[s] = row[(uint32_t)lane];
+          row += T;
+        }
+#pragma unroll
+        for (int s = 0; s < SMAX; ++s) N[s] = (kept >> s) & 1u ? n[s] : 0;
+      }
       while (c0 < n_listed && n_drawn <= kDrawn - kWave) {
         // ---- reaction SSA operator over [0, tau_k] ----
         const int rank = (int)__popcll(listed & below) - c0;
@@ -1098,13 +1134,13 @@ window_main_kernel(const StepArgs A) {
         const int j = ln & (GL - 1), grp = ln / GL;
         if (mine) {
 #pragma unroll
-          for (int s = 0; s < SMAX; ++s) items[rank * GL + s] = (uint32_t)N[s];
+          for (int s = 0; s < SMAX; ++s) moved_n[rank * GL + s] = N[s];
           L.npost[n_drawn + rank] = lane;  // space not yet in use
         }
         wave_sync();
         const bool run = c0 + grp < n_listed;
         const int Lt = run ? L.npost[n_drawn + grp] : 0;
-        int Nj = run && j < SMAX ? (int)items[ln] : 0;
+        int Nj = run && j < SMAX ? moved_n[ln] : 0;
         const double nav_t = lane_read(nav, Lt);
         const int reg_t = __builtin_amdgcn_ds_bpermute(4 * Lt, reg);
         const cptr<double> kw = as_const(rd->kcst) + reg_t * 32;
@@ -1142,6 +1178,7 @@ window_main_kernel(const StepArgs A) {
             if (!gone && (((mobile >> s) & 1) == 0 || apart) && N[s] != 0) atomicAdd(acc + (s * kWave + lane), N[s]);
             if (gone || apart) N[s] = 0;
           }
+          kept = apart ? 0u : kept & ~changed;
         }
         n_drawn += (int)__popcll(bi);
         c0 += kWave / GL;
@@ -1164,14 +1201,17 @@ window_main_kernel(const StepArgs A) {
           load_tet<SMAX>(there, k, S, width, lane, nxt);
         }
         __builtin_amdgcn_sched_barrier(0);
-        // Items in five classes, each species-major: more than 16 molecules
-        // (binomial face counts), so that few rounds wait on a binomial; then
-        // those of four, three, two and one Philox calls (13 to 16, ... 1 to 4
-        // molecules).  A round's lanes step through as many calls as its
-        // longest item has: with 5 to 16 molecules in one class the dendrite
-        // made 18.8 calls a tile, of which its items need 12.
-        // Where no tet has more than four of any species there is one class,
-        // listed without the search for it.
+        // Items in five classes: more than 16 molecules (binomial face counts),
+        // species-major, so that few rounds wait on a binomial and one that
+        // does has binomials of like length; then those of four, three, two
+        // and one Philox calls (13 to 16, ... 1 to 4 molecules), tet-major.  A
+        // round's lanes step through as many calls as its longest item has:
+        // with 5 to 16 molecules in one class the dendrite made 18.8 calls a
+        // tile, of which its items need 12.  Where no tet has more than four
+        // of any species there is one class.  (Found by a loop over classes
+        // and the species of each, the list took 5.9 us of the dendrite's 35
+        // a tile; by prefix sums of the lanes' class counts the window is 4%
+        // shorter, 6% at 480,000 tets with 20 molecules each.)
         renew<SMAX>(N);
         renew(lane);
         int mobile = (int)dmask;
@@ -1181,34 +1221,44 @@ window_main_kernel(const StepArgs A) {
           for (int s = 0; s < SMAX; ++s) {
             const bool has = N[s] > 0 && ((mobile >> s) & 1);
             const unsigned long long bs = __ballot(has);
-            if (has) items[n_item + (int)__popcll(bs & below)] = (uint32_t)(N[s] << 10) | (uint32_t)(lane << 4) | (uint32_t)s;
+            if (has) items[n_item + (int)__popcll(bs & below)] = (item_t)((N[s] << 10) | (lane << 4) | s);
             n_item += (int)__popcll(bs);
           }
         } else {
-          uint32_t sets[5] = {0u, 0u, 0u, 0u, 0u};  // species with any item of a class or of one before it
+          // the lane's items by class, eight bits each, from one call up
+          uint32_t held = 0u;
 #pragma unroll
           for (int s = 0; s < SMAX; ++s) {
-#pragma unroll
-            for (int cls = 0; cls < 5; ++cls)
-              sets[cls] |= __ballot(N[s] > kSmallM - 4 * cls) != 0ull ? 1u << s : 0u;
-          }
-#pragma unroll 1
-          for (int cls = 0; cls < 5; ++cls) {
-            const int lo = kSmallM - 4 * cls + 1;
-            const uint32_t span = cls == 0 ? 0x7fffffffu - (kSmallM + 1) : 3u;
-            uint32_t todo =
-                cls == 0 ? sets[0] : (cls == 1 ? sets[1] : (cls == 2 ? sets[2] : (cls == 3 ? sets[3] : sets[4])));
-            todo &= (uint32_t)mobile;
-#pragma unroll 1
-            for (; todo != 0u; todo &= todo - 1u) {
-              const int s = __builtin_ctz(todo);
-              const int n = N[s];
-              const bool has = (uint32_t)(n - lo) <= span;
-              const unsigned long long bs = __ballot(has);
-              if (has)
+            if (((mobile >> s) & 1) == 0) N[s] = 0;
+            const bool wide = N[s] > kSmallM;
+            const unsigned long long bs = __ballot(wide);
+            if (bs != 0ull) {
+              if (wide)
                 items[n_item + (int)__popcll(bs & below)] =
-                    ((uint32_t)(n < kPackedCount ? n : 0) << 10) | (uint32_t)(lane << 4) | (uint32_t)s;
+                    (item_t)(((N[s] < kPackedCount ? N[s] : 0) << 10) | (lane << 4) | s);
               n_item += (int)__popcll(bs);
+            }
+            const uint32_t u = (uint32_t)N[s] - 1u;
+            held += (u < (uint32_t)kSmallM ? 1u : 0u) << ((u << 1) & 24u);
+          }
+          // prefix sums over the lanes, sixteen bits a class
+          const uint32_t even = held & 0x00ff00ffu, odd = (held >> 8) & 0x00ff00ffu;
+          const uint32_t even_to = wave_prefix(even), odd_to = wave_prefix(odd);
+          const uint32_t even_all = (uint32_t)__builtin_amdgcn_readlane((int)even_to, kWave - 1);
+          const uint32_t odd_all = (uint32_t)__builtin_amdgcn_readlane((int)odd_to, kWave - 1);
+          const uint32_t at3 = (uint32_t)n_item, at2 = at3 + (odd_all >> 16), at1 = at2 + (even_all >> 16);
+          const uint32_t at0 = at1 + (odd_all & 0xffffu);
+          n_item = (int)(at0 + (even_all & 0xffffu));
+          const uint32_t e = even_to - even + (at0 | (at2 << 16)), o = odd_to - odd + (at1 | (at3 << 16));
+          unsigned long long next = (unsigned long long)((e & 0xffffu) | (o << 16)) |
+                                    ((unsigned long long)((e >> 16) | (o & 0xffff0000u)) << 32);
+#pragma unroll
+          for (int s = 0; s < SMAX; ++s) {
+            const uint32_t u = (uint32_t)N[s] - 1u;
+            if (u < (uint32_t)kSmallM) {
+              const uint32_t sh = (u << 2) & 48u;
+              items[(uint32_t)(next >> sh) & 0xffffu] = (item_t)((N[s] << 10) | (lane << 4) | s);
+              next += 1ull << sh;
             }
           }
         }
@@ -1226,14 +1276,14 @@ window_main_kernel(const StepArgs A) {
         if (r0 < n_drawn) {    // a round with items of changed species
           general = true;
           if (valid) {
-            const uint32_t itw = at < n_drawn ? (uint32_t)L.drawn[at] : items[at - n_drawn];
+            const uint32_t itw = at < n_drawn ? (uint32_t)L.drawn[at] : (uint32_t)items[at - n_drawn];
             Ln = (int)((itw >> 4) & 63);
             sp = (int)(itw & 15);
             m = at < n_drawn ? L.npost[at] : (int)(itw >> 10);
             nb = at < n_drawn ? L.nbar[at] : 0.0;
           }
         } else if (valid) {
-          const uint32_t itw = items[at - n_drawn];
+          const uint32_t itw = (uint32_t)items[at - n_drawn];
           Ln = (int)((itw >> 4) & 63);
           sp = (int)(itw & 15);
           m = (int)(itw >> 10);
@@ -1283,6 +1333,13 @@ window_main_kernel(const StepArgs A) {
       }
       n_drawn = 0;
       if (last) break;
+      // the counts are read again above: they are not held over the rounds
+#pragma unroll
+      for (int s = 0; s < SMAX; ++s) {
+        int n;
+        asm volatile("" : "=v"(n));
+        N[s] = n;
+      }
     }
     if (stepping) {
       // coalesced flush of the tile's own tets (other tiles add into them too);
