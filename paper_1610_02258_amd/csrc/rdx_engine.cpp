@@ -158,14 +158,6 @@ DevModel make_dev_model(const HostInstance& I) {
     const int b1 = (order == 2 && r1 >= 0) ? r1 : 0xff;
     m.info[r] = order | (b0 << 8) | (b1 << 16);
   }
-  // deps(r): reactions whose propensity reads a species that r changes
-  for (int r = 0; r < R; ++r) {
-    unsigned long long mask = 0;
-    for (int j = 0; j < R; ++j)
-      for (int s = 0; s < S; ++s)
-        if (m.delta[r][s] != 0 && I.lhs[(size_t)j * S + s] > 0) mask |= 1ull << j;
-    m.deps[r] = mask;
-  }
   return m;
 }
 
@@ -288,8 +280,7 @@ bool Engine::compatible(const HostInstance& I) const {
   if (I.S != S_ || I.R != R_) return false;
   const DevModel m = make_dev_model(I);
   return std::memcmp(m.info, model_host_.info, sizeof m.info) == 0 &&
-         std::memcmp(m.delta, model_host_.delta, sizeof m.delta) == 0 &&
-         std::memcmp(m.deps, model_host_.deps, sizeof m.deps) == 0;
+         std::memcmp(m.delta, model_host_.delta, sizeof m.delta) == 0;
 }
 
 rdx_status Engine::add_run(Run* r, hipStream_t stream) {
@@ -745,7 +736,6 @@ rdx_status Engine::sequence(const std::vector<Run*>& runs, hipStream_t stream) {
   a.S = S_;
   a.R = R_;
   a.model = model_;
-  std::memcpy(a.info, model_host_.info, sizeof a.info);
   {
     int32_t pair_of[32];
     listing_pairs(model_host_, a.pairs, &a.n_pairs, pair_of);

@@ -277,8 +277,7 @@ __device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
 // many at a time as the wave has groups.
 //
 // Diffusion items: every (tet, species) pair with something to sample becomes
-// an item; ballots pack them into LDS and they are sampled in rounds of 64,
-// one per lane.  Moves into the tile's own tets accumulate in LDS and are
+// an item; they are packed into LDS and sampled in rounds of 64, one per lane.  Moves into the tile's own tets accumulate in LDS and are
 // flushed once, coalesced; the rest are integer atomics into the next count
 // buffer.
 //
@@ -289,17 +288,18 @@ __device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
 // chunk could hold one run only, and the event blocks ended last wherever
 // tiles are few or runs small.  Here the tet is read once, listed, stepped and
 // diffused by the wave that holds it.  Per window, two launches against one:
-// 480,000 tets, 10 species, 2 molecules a tet 42.4 -> 36.7 us; 1.2 million
-// molecules in 60,000 tets of it 47.2 -> 28.9 us; 112,000 tets of the calcium
-// model with events crowded in one region 915 -> 320 us (with the binomial
-// search below 608 -> 320); 48 runs of 200 to 1,500 tets 59 -> 21 us.
+// 480,000 tets, 10 species, 2 molecules a tet 42.4 -> 35.1 us; a million
+// molecules in 60,000 tets of it 47.2 -> 21.0 us; 112,000 tets of the calcium
+// model with events crowded in one region 970 -> 220 us (by the binomial
+// search alone 608); a million tets of it 258 -> 223 us; 48 runs of 200 to
+// 1,500 tets 60 -> 19 us.
 //
 // What bounds a tile: the chain of a lone wave (a load, the propensities and a
-// Philox call, the item list, the items' draws), 10 us where tets hold two
+// Philox call, the item list, the items' draws), 9 us where tets hold two
 // molecules against 0.4 us of memory traffic at the copy rate, and VALU issue
-// where they hold hundreds (59% of the issue slots at the million-tet calcium
-// dendrite, 6,260 instructions a tile).  Hence waves per SIMD: four for up to
-// 12 species, three above.
+// where they hold hundreds (69% of the issue slots at the million-tet calcium
+// dendrite, 6,219 instructions a tile; 33% at two molecules, 1,129).  Hence
+// waves per SIMD: four for up to 12 species, three above.
 constexpr int kWave = 64;
 
 // Tables the window kernels only read -- the run table, the tile map, the
@@ -371,10 +371,10 @@ __device__ __forceinline__ void renew_s(uint32_t& a, uint32_t& b) { asm volatile
 // the face couplings.
 //
 // The per-molecule draws of an item (m <= 16) are the words w0, w0 + 1, ...
-// of its species stream, w0 the words the rounding used (0 or 1); word j is
-// word j mod 4 of Philox call j / 4, so an item takes at most five calls,
-// which its own lane makes, testing the words against the item's
-// probabilities.  (With m > npost the cap can bind in the middle of the
+// of its species stream, w0 the words the rounding used (0 or 1; a rounding
+// word is counted with the others and taken back); word j is word j mod 4 of
+// Philox call j / 4, so an item takes at most five calls, which its own lane
+// makes, testing the words against the item's probabilities.  (With m > npost the cap can bind in the middle of the
 // walk; such an item -- only a species changed in the window can have one --
 // is walked word by word in stream order.)
 constexpr int kSmallM = 16;
@@ -916,8 +916,8 @@ window_main_kernel(const StepArgs A) {
   const int step_word = as_const(A.step_words)[A.parity];
   const int width = 1 << A.tile_shift;  // tets of a tile
   const int n_tiles = *as_const(A.n_tiles) << (6 - A.tile_shift);
-  asm volatile("" ::"s"(step_word), "s"(n_tiles), "s"(A.S), "s"(A.info[4]), "s"(A.info[20]), "s"(A.n_pairs),
-               "s"(A.pairs[12]), "s"(A.tile_claim));
+  asm volatile("" ::"s"(step_word), "s"(n_tiles), "s"(A.S), "s"(A.n_pairs), "s"(A.pairs[8]), "s"(A.pairs[24]),
+               "s"(A.tile_claim));
   const int k = A.step >= 0 ? A.step : step_word;
   const int b = blockIdx.x, G = gridDim.x;
   if (b == 0) {

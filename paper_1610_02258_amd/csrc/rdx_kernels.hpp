@@ -16,13 +16,11 @@ namespace rdx {
 // Reaction tables shared by the runs of a batch (one device copy).  info[r]
 // packs reaction r's order (bits 0-7) and reactant species r0, r1 (bits 8-15,
 // 16-23; 0xff if absent; r0 == r1 for a homodimer) in one dword so that
-// uniform reads are scalar loads.  delta[r][s] is the net change of species
-// s, deps[r] the reactions whose propensity reads a species r changes.
+// a lane's reaction is one load.  delta[r][s] is the net change of species s.
 struct alignas(16) DevModel {
   int32_t S, R, pad0, pad1;
   int32_t info[32];
   int8_t delta[32][16];
-  unsigned long long deps[32];
 };
 
 // Listing coefficients of one region: a_0 regrouped as
@@ -73,7 +71,6 @@ struct StepArgs {
   int32_t tile_shift;          // a block's tile: 1 << tile_shift tets, an entry of the tile map cut in equal parts
   int32_t single_run;          // 1: one run, tile t is (run 0, first tet 64 t) without the tile map
   const DevModel* model;
-  int32_t info[32];            // = model->info, in kernel arguments for scalar loads
   int32_t n_pairs;             // distinct reactant pairs of the second-order reactions
   int32_t pairs[32];           // a | b << 8 | (a == b) << 16
   // tiles claimed at run time: after its first (static) tile, a block takes
