@@ -589,9 +589,12 @@ static int os_cr_select(const double* a, int R, double a0, os_stream* st)
   int n = 0;
   for (int r = 0; r < R; ++r)
     if (a[r] > 0.0 && os_expfield(a[r]) == chosen) n++;
-  uint64_t bbits = (uint64_t)(chosen + 1) << 52;  /* 2^(chosen-1022): group upper bound */
-  double bound;
-  memcpy(&bound, &bbits, sizeof bound);
+  /* half the group's upper bound 2^(chosen-1022), against half the propensity
+     (both exact): the bound of the largest finite group would be infinite and
+     never accept; an infinite propensity is accepted at once */
+  uint64_t hbits = chosen == 0x7ff ? 0 : (uint64_t)chosen << 52;
+  double half;
+  memcpy(&half, &hbits, sizeof half);
   for (;;) {
     double u2 = os_u53_co(st);
     int j = (int)(u2 * (double)n);
@@ -603,7 +606,7 @@ static int os_cr_select(const double* a, int R, double a0, os_stream* st)
         if (seen == j) break;
         seen++;
       }
-    if (u3 * bound < a[r]) return r;
+    if (u3 * half < 0.5 * a[r]) return r;
   }
 }
 

@@ -833,7 +833,7 @@ __device__ __forceinline__ unsigned int ssa_window(TileLds<SMAX, RMAX>& L, doubl
       if (dt + t_reac > tau) break;
       ++call;
       double left = u23 * a0;
-      int g = 0x7ff;  // exponent field of the group
+      int g = 0x800;  // exponent field of the group, at first above any (0x7ff: infinite propensities)
       uint32_t members = 0;
       for (;;) {  // the groups from the largest exponent down
         int e = 0;
@@ -855,7 +855,10 @@ __device__ __forceinline__ unsigned int ssa_window(TileLds<SMAX, RMAX>& L, doubl
         left = left - sum;
       }
       const double n = (double)__popc(members);
-      const double bound = __longlong_as_double((long long)(g + 1) << 52);
+      // u < a / 2^(g - 1022), both sides halved (which is exact): the bound of
+      // the largest finite group would be infinite, and no attempt accepted.
+      // An infinite propensity is accepted at once.
+      const double half = g == 0x7ff ? 0.0 : __longlong_as_double((long long)g << 52);
       int rn = 0;
       for (;;) {  // the attempts of all calls in hand at once; the first accepted one counts
         int q = (int)(draws.u01 * n);
@@ -863,7 +866,7 @@ __device__ __forceinline__ unsigned int ssa_window(TileLds<SMAX, RMAX>& L, doubl
         uint32_t m = members;
         for (; q > 0; --q) m &= m - 1u;
         const int r = __builtin_ctz(m);
-        const bool accept = draws.first + (uint32_t)j >= call && draws.u23 * bound < a[r];
+        const bool accept = draws.first + (uint32_t)j >= call && draws.u23 * half < 0.5 * a[r];
         const uint32_t acc = (uint32_t)(__ballot(accept) >> g0) & group;
         if (acc != 0u) {
           const int w = __builtin_ctz(acc);
