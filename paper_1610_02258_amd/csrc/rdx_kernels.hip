@@ -1045,9 +1045,10 @@ window_main_kernel(const StepArgs A) {
     // t_reac = -ln(u) / a0 <= tau_k, and -ln(u) >= 1 - u; so a tet whose first
     // uniform u of the window has 1 - u above a0 tau_k (with a relative
     // margin of 1e-6, far above the rounding of a0, of ln and of the
-    // division) has no event, and every other tet with a0 > 0 is listed.  A
-    // listed tet without an event is harmless: its SSA ends at the first draw
-    // and its items are those of an unlisted tet.
+    // division) has no event, and every other tet with a0 > 0 is listed, or
+    // whose a0 is indefinite (constants that sum to infinity, of an absent
+    // species).  A listed tet without an event is harmless: its SSA ends at the
+    // first draw and its items are those of an unlisted tet.
     bool event = false;
     double a0 = 0.0;
     if (active) {
@@ -1077,7 +1078,7 @@ window_main_kernel(const StepArgs A) {
     const bool early = (int)__popcll(__ballot(tau * a0 > 0.5)) <= 2 * (kWave / GL);
     if (early) claim_next();
     {
-      if (a0 > 0.0) {
+      if (!(a0 <= 0.0)) {
         uint32_t w0 = 0u, w1 = 0u, w2 = (uint32_t)i, w3 = window;
         philox4x32_10(w0, w1, w2, w3, key0, key1);
         event = !(1.0 - u53_oc(w0, w1) > (tau * a0) * 1.000001);
