@@ -318,9 +318,9 @@ rdx_status Engine::add_run(Run* r, hipStream_t stream) {
   std::vector<double> geo(4 * T);
   for (size_t i = 0; i < T; ++i) {
     geo[4 * i + 0] = I.G[i];
-    geo[4 * i + 1] = I.cum[4 * i + 0];
-    geo[4 * i + 2] = I.cum[4 * i + 1];
-    geo[4 * i + 3] = I.cum[4 * i + 2];
+    // a share that couplings without a finite sum leave indefinite is below no
+    // draw: as a share of 0, everything goes to the last face
+    for (size_t k = 0; k < 3; ++k) geo[4 * i + 1 + k] = I.cum[4 * i + k] > 0.0 ? I.cum[4 * i + k] : 0.0;
   }
   const std::vector<double> kc = rate_image(model_host_, I);
   hipError_t e = hipMemcpyAsync(r->nbr, I.nbr.data(), 16 * T, hipMemcpyHostToDevice, stream);

@@ -1304,7 +1304,8 @@ window_main_kernel(const StepArgs A) {
         if (valid) {
           const int4 tnb = L.nbr[Ln];
           const double2 g0 = L.geo[0][Ln], g1 = L.geo[1][Ln];
-          const ItemGeo geo{fmin(L.tauD[sp] * g0.x, 1.0), g0.y, g1.x, g1.y};
+          // 0 x infinity (no leaving) is not 1: zero is the larger of it and zero
+          const ItemGeo geo{fmin(fmax(L.tauD[sp] * g0.x, 0.0), 1.0), g0.y, g1.x, g1.y};
           const uint32_t tet = (uint32_t)(base + Ln);
           int draws = m;
           DrawCounts c(geo);
