@@ -1034,11 +1034,11 @@ window_main_kernel(const StepArgs A) {
 #pragma unroll
     for (int s = 0; s < SMAX; ++s) N[s] = cur.N[s];
     int errbits = 0;
-    int most = 0;
+    uint32_t most = 0u;  // (a count that wrapped past 2^31 is above the cap, too)
 #pragma unroll
-    for (int s = 0; s < SMAX; ++s) most = N[s] > most ? N[s] : most;
-    if (most > kCountCap) errbits |= kErrOverflow;
-    const bool any_wide = __ballot(most >= kPackedCount) != 0ull;
+    for (int s = 0; s < SMAX; ++s) most = (uint32_t)N[s] > most ? (uint32_t)N[s] : most;
+    if (most > (uint32_t)kCountCap) errbits |= kErrOverflow;
+    const bool any_wide = __ballot(most >= (uint32_t)kPackedCount) != 0ull;
 
     // ---- listing ----
     // The window's first SSA event falls inside [0, tau_k] only if
@@ -1220,7 +1220,7 @@ window_main_kernel(const StepArgs A) {
         renew(lane);
         int mobile = (int)dmask;
         renew_s(mobile);
-        if (__ballot(most > 4) == 0ull) {
+        if (__ballot(most > 4u) == 0ull) {
 #pragma unroll
           for (int s = 0; s < SMAX; ++s) {
             const bool has = N[s] > 0 && ((mobile >> s) & 1);
