@@ -212,7 +212,7 @@ struct FenceOnExit {
 Engine::~Engine() {
   drain();
   if (staged_) (void)hipEventSynchronize(staged_);
-  free_graphs();
+  graphs_.clear([](hipGraphExec_t g) { (void)hipGraphExecDestroy(g); });
   if (capture_stream_) (void)hipStreamDestroy(capture_stream_);
   if (own_) (void)hipStreamDestroy(own_);
   for (hipEvent_t e : marks_) (void)hipEventDestroy(e);
@@ -236,9 +236,9 @@ Engine::~Engine() {
   if (h_n_tiles_) (void)hipHostFree(h_n_tiles_);
 }
 
-void Engine::free_graphs() {
-  for (auto& g : graphs_) (void)hipGraphExecDestroy(g.second);
-  graphs_.clear();
+void Engine::wait_idle(hipStream_t stream) {
+  fence(stream);
+  for (auto& f : fences_) (void)hipEventSynchronize(f.second);
 }
 
 rdx_status Engine::init(const HostInstance& proto, size_t arena_bytes, int max_runs, int64_t max_tets) {
@@ -633,6 +633,7 @@ rdx_status Engine::launch_plain(const StepArgs& a0, int64_t step0, int64_t K, hi
     }
     hipError_t e = launch_window(a, stream, marks);
     if (e != hipSuccess) return set_error(RDX_EHIP, std::string("window launch: ") + hipGetErrorString(e));
+    k_now_ = step0 + k + 1;
     if (rec_on_ && (k + 1) % rec_.every == 0) {
       // the counts after this window sit in buffer (window + k + 1) & 1 (the
       // run's window index advances when the sequence ends); the next window
@@ -649,39 +650,43 @@ rdx_status Engine::launch_plain(const StepArgs& a0, int64_t step0, int64_t K, hi
   return RDX_OK;
 }
 
-rdx_status Engine::launch_graphs(const StepArgs& a0, int64_t step0, int64_t reps, hipStream_t stream) {
+rdx_status Engine::launch_graphs(const StepArgs& a0, int64_t step0, int64_t reps, bool replay, hipStream_t stream) {
   const int W = shape_.graph_windows;
-  for (int64_t r = 0; r < std::max<int64_t>(1, reps); ++r) {
-    const int parity = (int)((step0 + r * W) & 1);
+  const int parity = (int)(step0 & 1);
+  const int n = (W & 1) != 0 && reps > 1 ? 2 : 1;  // graphs of an odd length alternate
+  GraphCache<hipGraphExec_t>::Key keys[2];
+  for (int j = 0; j < n; ++j)
     // everything of the arguments that can change between sequences is in the
     // key (pointers and tables are fixed for the engine's life)
-    const long long shape_key = ((long long)a0.grid << 6) | ((long long)a0.tile_shift << 3) | ((long long)(a0.tile_claim ? 1 : 0) << 2) |
-                                ((long long)parity << 1) | (long long)a0.single_run;
-    const auto key = std::make_pair(W, shape_key);
-    auto it = graphs_.find(key);
-    if (it == graphs_.end()) {
-      if (graphs_.size() >= 16) free_graphs();
-      if (!capture_stream_) RDX_HIP(hipStreamCreateWithFlags(&capture_stream_, hipStreamNonBlocking));
-      // W windows, captured once on a private stream; each reads its step
-      // index from the word that the window before it wrote
-      StepArgs a = a0;
-      a.step = -1;
-      RDX_HIP(hipStreamBeginCapture(capture_stream_, hipStreamCaptureModeThreadLocal));
-      hipError_t e = hipSuccess;
-      for (int k = 0; k < W && e == hipSuccess; ++k) {
-        a.parity = (parity + k) & 1;
-        e = launch_window(a, capture_stream_, nullptr);
-      }
-      hipGraph_t graph = nullptr;
-      hipError_t e2 = hipStreamEndCapture(capture_stream_, &graph);
-      if (e == hipSuccess) e = e2;
-      hipGraphExec_t exec = nullptr;
-      if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-      if (graph) (void)hipGraphDestroy(graph);
-      if (e != hipSuccess) return set_error(RDX_EHIP, std::string("graph capture: ") + hipGetErrorString(e));
-      it = graphs_.emplace(key, exec).first;
+    keys[j] = {W, ((long long)a0.grid << 6) | ((long long)a0.tile_shift << 3) | ((long long)(a0.tile_claim ? 1 : 0) << 2) |
+                      ((long long)(parity ^ j) << 1) | (long long)a0.single_run};
+  // W windows, captured once on a private stream; each reads its step index
+  // from the word that the window before it wrote
+  auto capture = [&](int j, hipGraphExec_t* exec) -> int {
+    if (!capture_stream_) RDX_HIP(hipStreamCreateWithFlags(&capture_stream_, hipStreamNonBlocking));
+    StepArgs a = a0;
+    a.step = -1;
+    RDX_HIP(hipStreamBeginCapture(capture_stream_, hipStreamCaptureModeThreadLocal));
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < W && e == hipSuccess; ++k) {
+      a.parity = (parity + j + k) & 1;
+      e = launch_window(a, capture_stream_, nullptr);
     }
-    if (r < reps) RDX_HIP(hipGraphLaunch(it->second, stream));
+    hipGraph_t graph = nullptr;
+    hipError_t e2 = hipStreamEndCapture(capture_stream_, &graph);
+    if (e == hipSuccess) e = e2;
+    if (e == hipSuccess) e = hipGraphInstantiate(exec, graph, nullptr, nullptr, 0);
+    if (graph) (void)hipGraphDestroy(graph);
+    if (e != hipSuccess) return set_error(RDX_EHIP, std::string("graph capture: ") + hipGetErrorString(e));
+    return RDX_OK;
+  };
+  hipGraphExec_t execs[2] = {nullptr, nullptr};
+  const int st = graphs_.take(keys, n, execs, capture, [&] { wait_idle(stream); },
+                              [](hipGraphExec_t g) { (void)hipGraphExecDestroy(g); });
+  if (st != RDX_OK) return (rdx_status)st;
+  for (int64_t r = 0; replay && r < reps; ++r) {
+    RDX_HIP(hipGraphLaunch(execs[n == 2 ? r & 1 : 0], stream));
+    k_now_ = step0 + (r + 1) * W;
   }
   return RDX_OK;
 }
@@ -722,6 +727,7 @@ rdx_status Engine::sequence(const std::vector<Run*>& runs, hipStream_t stream) {
     if (K >= kStepRebase) return set_error(RDX_EINVAL, "sequence too long");
     k0 = k_now_ & 1;  // keep the parity of the claim counters
     RDX_HIP(launch_set_step(d_step_, (int32_t)k0, stream));
+    k_now_ = k0;
   }
   int64_t n_tiles = 0;
   rdx_status st = upload_tables(active, k0, stream, &n_tiles);
@@ -752,7 +758,7 @@ rdx_status Engine::sequence(const std::vector<Run*>& runs, hipStream_t stream) {
     int64_t in_graphs = 0;
     if (!timing_ && sh.graph_windows > 1 && n >= sh.graph_windows) {
       in_graphs = n / sh.graph_windows * sh.graph_windows;
-      r = launch_graphs(a, k0 + at, n / sh.graph_windows, stream);
+      r = launch_graphs(a, k0 + at, n / sh.graph_windows, true, stream);
     }
     if (r == RDX_OK) r = launch_plain(a, k0 + at + in_graphs, n - in_graphs, stream);
     shape_ = keep;
@@ -773,7 +779,7 @@ rdx_status Engine::sequence(const std::vector<Run*>& runs, hipStream_t stream) {
       cover(n_tiles, c, &a);
       const ExecShape keep = shape_;
       shape_ = c;
-      st = launch_graphs(a, k0 + done, 0, stream);
+      st = launch_graphs(a, k0 + done, n / c.graph_windows, false, stream);
       shape_ = keep;
       if (st != RDX_OK) return st;
     }
@@ -807,7 +813,6 @@ rdx_status Engine::sequence(const std::vector<Run*>& runs, hipStream_t stream) {
     st = run_chunk(shape_, done, K - done);
     if (st != RDX_OK) return st;
   }
-  k_now_ = k0 + K;
 
   for (Run* r : active) {
     r->t = r->plan_t_after;

@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "rdx.h"
+#include "rdx_graphs.hpp"
 #include "rdx_internal.hpp"
 #include "rdx_kernels.hpp"
 
@@ -211,12 +212,13 @@ class Engine {
  private:
   rdx_status upload_tables(const std::vector<Run*>& active, int64_t k0, hipStream_t stream,
                            int64_t* n_tiles_out);
-  // K windows, or `reps` graphs of windows (0: only captured), from step index
-  // `step0` on
+  // K windows, or `reps` graphs of windows, from step index `step0` on; the
+  // graphs are captured first, and with `replay` false no more than that
   rdx_status launch_plain(const StepArgs& a, int64_t step0, int64_t K, hipStream_t stream);
-  rdx_status launch_graphs(const StepArgs& a, int64_t step0, int64_t reps, hipStream_t stream);
+  rdx_status launch_graphs(const StepArgs& a, int64_t step0, int64_t reps, bool replay, hipStream_t stream);
   void cover(int64_t n_tiles, const ExecShape& sh, StepArgs* a) const;
-  void free_graphs();
+  // Waits for all work enqueued so far, the sequence under way on `stream` included.
+  void wait_idle(hipStream_t stream);
 
   int S_ = 0, R_ = 0;
   DevModel model_host_{};
@@ -247,15 +249,15 @@ class Engine {
   hipEvent_t reset_staged_ = nullptr;
   std::vector<const Run*> tile_runs_;  // runs of the tile map on the device
   std::vector<int64_t> tile_run_T_;
-  int64_t k_now_ = 0;                  // batch step index == d_step_[k_now_ & 1]
+  int64_t k_now_ = 0;                  // batch step index == d_step_[k_now_ & 1], kept launch by launch
 
-  // graphs by (windows, grids); captured on a private stream
+  // captured on a private stream
   hipStream_t capture_stream_ = nullptr;
   hipStream_t own_ = nullptr;
   std::vector<std::pair<hipStream_t, hipEvent_t>> fences_;
   RecordHook rec_{};
   bool rec_on_ = false;
-  std::map<std::pair<int, long long>, hipGraphExec_t> graphs_;
+  GraphCache<hipGraphExec_t> graphs_;
 
   ExecShape shape_;
   bool tuning_ = false;
