@@ -211,7 +211,7 @@ rdx_status rdx_get_geometry(const rdx_sim* sim, int32_t* nbr, double* g, double*
 
 /* The same set-up arrays and tau computed on the host only, without creating
  * a simulation or touching a GPU (same layouts as rdx_get_geometry; *tau
- * receives the window).  Errors as rdx_create except RDX_ENOMEM/RDX_EHIP. */
+ * receives the window).  Errors as rdx_create except RDX_EHIP. */
 rdx_status rdx_setup_geometry(const rdx_mesh* mesh, const rdx_model* model, double tau_override,
                               int32_t* nbr, double* g, double* G, double* cum, double* nav,
                               double* tau);

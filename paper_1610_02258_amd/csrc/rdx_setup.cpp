@@ -12,6 +12,7 @@
 #include <array>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <numeric>
 
 #include "rdx_internal.hpp"
@@ -62,8 +63,10 @@ struct FaceRecord {
 
 }  // namespace
 
-rdx_status build_instance(const rdx_mesh* mesh, const rdx_model* model, double tau_override,
-                          HostInstance* out, std::string* err) {
+namespace {
+
+rdx_status build_checked(const rdx_mesh* mesh, const rdx_model* model, double tau_override,
+                         HostInstance* out, std::string* err) {
   if (!mesh || !model || !out) {
     *err = "null mesh, model or output";
     return RDX_EINVAL;
@@ -203,26 +206,49 @@ rdx_status build_instance(const rdx_mesh* mesh, const rdx_model* model, double t
       int32_t tf;    // 4 tet + face
     };
     const size_t n = 4 * (size_t)T;
-    std::vector<int32_t> least(n);
-    std::vector<uint64_t> rest(n);
+    // A tet's vertices in ascending order, vertex * 4 + its place in the tet:
+    // the faces opposite the first to the last are (1, 2, 3), (0, 2, 3), (0, 1,
+    // 3) and (0, 1, 2) of them.  Ordered again in the second pass, so that the
+    // faces (64 bytes a tet) are the only array of their size.
+    auto ordered = [&](size_t i, uint64_t v[4]) {
+      for (uint64_t k = 0; k < 4; ++k) v[k] = ((uint64_t)(uint32_t)tets[4 * i + k] << 2) | k;
+      auto in_order = [&](int a, int b) {
+        const uint64_t lo = std::min(v[a], v[b]), hi = std::max(v[a], v[b]);
+        v[a] = lo;
+        v[b] = hi;
+      };
+      in_order(0, 1);
+      in_order(2, 3);
+      in_order(0, 2);
+      in_order(1, 3);
+      in_order(1, 2);
+    };
+    uint64_t v[4];
     std::vector<int32_t> end((size_t)mesh->n_verts + 1, 0);
-    for (size_t f = 0; f < n; ++f) {
-      const int32_t* tv = tets + (f & ~(size_t)3);
-      const int32_t a = tv[kFace[f & 3][0]], b = tv[kFace[f & 3][1]], c = tv[kFace[f & 3][2]];
-      const int32_t lo = std::min(a, b), hi = std::max(a, b);
-      least[f] = std::min(lo, c);
-      rest[f] = ((uint64_t)std::min(std::max(lo, c), hi) << 32) | (uint64_t)std::max(hi, c);
-      ++end[(size_t)least[f] + 1];
+    for (size_t i = 0; i < (size_t)T; ++i) {
+      ordered(i, v);
+      end[(size_t)(v[0] >> 2) + 1] += 3;
+      ++end[(size_t)(v[1] >> 2) + 1];
     }
-    for (size_t v = 0; v < (size_t)mesh->n_verts; ++v) end[v + 1] += end[v];
+    for (size_t q = 0; q < (size_t)mesh->n_verts; ++q) end[q + 1] += end[q];
     std::vector<Rest> faces(n);
-    // filled in order of the faces, end[v] moves from bucket v's start to its end
-    for (size_t f = 0; f < n; ++f) faces[(size_t)end[(size_t)least[f]]++] = Rest{rest[f], (int32_t)f};
+    // end[q] moves from bucket q's start to its end
+    for (size_t i = 0; i < (size_t)T; ++i) {
+      ordered(i, v);
+      auto put = [&](int least, int mid, int most, int opposite) {
+        faces[(size_t)end[(size_t)(v[least] >> 2)]++] =
+            Rest{((v[mid] >> 2) << 32) | (v[most] >> 2), (int32_t)(4 * i + (size_t)(v[opposite] & 3))};
+      };
+      put(1, 2, 3, 0);
+      put(0, 2, 3, 1);
+      put(0, 1, 3, 2);
+      put(0, 1, 2, 3);
+    }
     size_t from = 0;
-    for (size_t v = 0; v < (size_t)mesh->n_verts && faces_ok; ++v) {
+    for (size_t q = 0; q < (size_t)mesh->n_verts && faces_ok; ++q) {
       Rest* const b = faces.data() + from;
-      const size_t m = (size_t)end[v] - from;
-      from = (size_t)end[v];
+      const size_t m = (size_t)end[q] - from;
+      from = (size_t)end[q];
       if (m < 2) continue;
       if (m <= 64) {
         for (size_t x = 1; x < m; ++x) {
@@ -329,6 +355,19 @@ rdx_status build_instance(const rdx_mesh* mesh, const rdx_model* model, double t
     I.tau = 1.0 / dmax;
   }
   return RDX_OK;
+}
+
+}  // namespace
+
+rdx_status build_instance(const rdx_mesh* mesh, const rdx_model* model, double tau_override,
+                          HostInstance* out, std::string* err) {
+  try {
+    return build_checked(mesh, model, tau_override, out, err);
+  } catch (const std::bad_alloc&) {  // nothing is thrown across the C ABI
+    if (out) *out = HostInstance{};
+    *err = "out of memory";  // (short enough to need none itself)
+    return RDX_ENOMEM;
+  }
 }
 
 }  // namespace rdx
