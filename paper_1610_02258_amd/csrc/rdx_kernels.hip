@@ -1060,13 +1060,25 @@ window_main_kernel(const StepArgs A) {
       if (rd->region == nullptr) {
         a0 = listing_rate<SMAX>(A, as_const(rd->lcoef), NV, nav);
       } else {
-        // one region of the tile at a time (neighbouring tets mostly share one)
-        unsigned long long left = __ballot(true);
-        while (left != 0ull) {
-          const int q = __builtin_amdgcn_readlane(reg, __builtin_ctzll(left));
-          const double r = listing_rate<SMAX>(A, as_const(rd->lcoef) + q * kLStride, NV, nav);
-          if (reg == q) a0 = r;
-          left &= ~__ballot(reg == q);
+        // One region of the tile at a time, its coefficients by scalar loads,
+        // where there are one or two (neighbouring tets mostly share one); else
+        // each tet with loads of its own.  A window of 480,000 tets of 8 species
+        // and 8 reactions, labels drawn at random from 2, 3, 4 and 8 regions: a
+        // pass for each 37.3, 40.0, 51.5, 52.9 us, by this rule 36.2, 36.5, 37.6,
+        // 36.4; with one region 35.3.
+        const unsigned long long all = __ballot(true);
+        const int q0 = __builtin_amdgcn_readlane(reg, __builtin_ctzll(all));
+        unsigned long long left = __ballot(reg != q0);
+        const int q1 = __builtin_amdgcn_readlane(reg, __builtin_ctzll(left != 0ull ? left : all));
+        left = __ballot(reg != q0 && reg != q1);
+        if (left == 0ull) {
+          for (int q = q0;; q = q1) {
+            const double r = listing_rate<SMAX>(A, as_const(rd->lcoef) + q * kLStride, NV, nav);
+            if (reg == q) a0 = r;
+            if (q == q1) break;
+          }
+        } else {
+          a0 = listing_rate<SMAX>(A, as_const(rd->lcoef) + reg * kLStride, NV, nav);
         }
       }
     }
