@@ -28,6 +28,7 @@ namespace {
 constexpr int kRecThreads = 256;
 constexpr int kRecUnroll = 4;
 constexpr int kRecMaxBlocks = 4096;  // all species together
+constexpr int kRecFewBlocks = 256;   // up to here a lane takes four tets in all
 constexpr int kRecMaxRegions = 8;
 constexpr int kRecMaxSpecies = 16;
 
@@ -50,7 +51,12 @@ typedef unsigned uint4_row __attribute__((ext_vector_type(4), aligned(4)));
 // a 4-byte and a 1-byte load per tet, four tets in flight, a record of a
 // million tets of 15 species took 19.2 us, now 16.7, of which this kernel has
 // 12.7 (61 MB, 4.8 TB/s).
-template <int NR>
+//
+// U loads of a lane at a time: four, or one where a block a CU then has every
+// tet.  There the adds of the loads past the end are what is felt (eight
+// accumulators, 128 adds a load): 1,296 and 15,288 tets of 16 species in eight
+// regions 12.90 and 12.96 us a record with four, 12.31 and 12.58 with one.
+template <int NR, int U>
 __global__ __launch_bounds__(kRecThreads) void region_counts_kernel(
     const int32_t* __restrict__ counts, const uint8_t* __restrict__ region, int T, int S,
     int n_regions, unsigned long long* __restrict__ partial) {
@@ -66,17 +72,17 @@ __global__ __launch_bounds__(kRecThreads) void region_counts_kernel(
   };
   const uint32_t* const labels = reinterpret_cast<const uint32_t*>(region);
   const int64_t stride = (int64_t)gridDim.x * kRecThreads, quads = T / 4;
-  for (int64_t t = (int64_t)blockIdx.x * kRecThreads + threadIdx.x; t < quads; t += kRecUnroll * stride) {
-    uint4_row v[kRecUnroll];
-    uint32_t g[kRecUnroll];
+  for (int64_t t = (int64_t)blockIdx.x * kRecThreads + threadIdx.x; t < quads; t += U * stride) {
+    uint4_row v[U];
+    uint32_t g[U];
 #pragma unroll
-    for (int k = 0; k < kRecUnroll; ++k) {  // past the end: the last quad, without effect
+    for (int k = 0; k < U; ++k) {  // past the end: the last quad, without effect
       const int64_t at = t + k * stride < quads ? t + k * stride : quads - 1;
       v[k] = *reinterpret_cast<const uint4_row*>(c + 4 * at);
       g[k] = NR > 1 ? labels[at] : 0u;
     }
 #pragma unroll
-    for (int k = 0; k < kRecUnroll; ++k) {
+    for (int k = 0; k < U; ++k) {
       const bool in = t + k * stride < quads;
 #pragma unroll
       for (int e = 0; e < 4; ++e) add(in ? v[k][e] : 0u, (g[k] >> (8 * e)) & 0xffu);
@@ -135,10 +141,16 @@ __global__ __launch_bounds__(kRecThreads) void region_sums_finish_kernel(
 // device.
 static __device__ __align__(256) unsigned long long scratch[kRegionScratchBytes / sizeof(unsigned long long)];
 
+// Whether a block a CU has every tet with one load of a lane.
+bool few_blocks(int32_t T, int32_t S) {
+  return ((int64_t)T + 4 * kRecThreads - 1) / (4 * kRecThreads) * S <= kRecFewBlocks;
+}
+
 // Slots the region-sum kernels write for (T, S): nb blocks per species, one
 // slot of kRecMaxRegions sums per block.
 int region_blocks(int32_t T, int32_t S) {
-  const int64_t want = ((int64_t)T + 4 * kRecThreads * kRecUnroll - 1) / (4 * kRecThreads * kRecUnroll);
+  const int64_t tets = few_blocks(T, S) ? 4 * kRecThreads : 4 * kRecThreads * kRecUnroll;  // of a block, at a time
+  const int64_t want = ((int64_t)T + tets - 1) / tets;
   const int64_t cap = kRecMaxBlocks / S > 0 ? kRecMaxBlocks / S : 1;
   int nb = (int)(want < cap ? want : cap);
   // workgroups go to the 8 XCDs round-robin by linear id (x + s nb): with nb
@@ -189,14 +201,14 @@ hipError_t launch_region_counts(const int32_t* counts, const uint8_t* region, in
   const dim3 grid((unsigned)nb, (unsigned)S);
   // the fewest accumulators that hold every region: each costs a compare and
   // a 64-bit add per tet
-  if (n_regions > 4)
-    region_counts_kernel<8><<<grid, kRecThreads, 0, stream>>>(counts, region, T, S, n_regions, scratch);
-  else if (n_regions > 2)
-    region_counts_kernel<4><<<grid, kRecThreads, 0, stream>>>(counts, region, T, S, n_regions, scratch);
-  else if (n_regions == 2)
-    region_counts_kernel<2><<<grid, kRecThreads, 0, stream>>>(counts, region, T, S, n_regions, scratch);
-  else
-    region_counts_kernel<1><<<grid, kRecThreads, 0, stream>>>(counts, nullptr, T, S, 1, scratch);
+  auto launch = [&](auto one, auto all) {
+    (few_blocks(T, S) ? one : all)<<<grid, kRecThreads, 0, stream>>>(counts, n_regions > 1 ? region : nullptr, T, S,
+                                                                     n_regions, scratch);
+  };
+  if (n_regions > 4) launch(&region_counts_kernel<8, 1>, &region_counts_kernel<8, kRecUnroll>);
+  else if (n_regions > 2) launch(&region_counts_kernel<4, 1>, &region_counts_kernel<4, kRecUnroll>);
+  else if (n_regions == 2) launch(&region_counts_kernel<2, 1>, &region_counts_kernel<2, kRecUnroll>);
+  else launch(&region_counts_kernel<1, 1>, &region_counts_kernel<1, kRecUnroll>);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   region_sums_finish_kernel<<<S, kRecThreads, 0, stream>>>(scratch, nb, S, n_regions, out);
