@@ -684,15 +684,19 @@ struct LaneReaction {
 
 // Items of changed species a tile holds at a time: a chunk of listed tets adds
 // up to 64 to what waits.
-constexpr int kDrawn = 96;
+template <int SMAX, int RMAX>
+constexpr int drawn_items() {
+  return SMAX > 12 && RMAX > 24 ? 88 : 96;
+}
 
 // LDS of a block: this part, of one size in an instance ...
 template <int SMAX, int RMAX>
 struct TileLds {
   // items of the species events changed: mean occupancy, post-reaction count,
   // lane << 4 | species
+  static constexpr int kDrawn = drawn_items<SMAX, RMAX>();
   double nbar[kDrawn];
-  int npost[kDrawn];
+  int npost[SMAX <= 12 ? kDrawn : 1];  // (above 12 species at the end of tile_rows)
   uint16_t drawn[kDrawn];
   int ctr, sub_lo, sub_hi;  // the block's claim counter (index) and sub-range
   int8_t delta[RMAX][16];  // net changes by reaction and species
@@ -718,12 +722,29 @@ constexpr int ssa_row_bytes() {
   return kWave / ssa_lanes<SMAX, RMAX>() * RMAX * (int)sizeof(double);
 }
 template <int SMAX, int RMAX>
-constexpr int tile_row_bytes(int S) {
-  constexpr int least = ssa_row_bytes<SMAX, RMAX>() > kWave * (int)sizeof(int) ? ssa_row_bytes<SMAX, RMAX>()
-                                                                               : kWave * (int)sizeof(int);
+__host__ __device__ constexpr int tile_row_bytes(int S) {
+  constexpr int ssa = ssa_row_bytes<SMAX, RMAX>() > kWave * (int)sizeof(int) ? ssa_row_bytes<SMAX, RMAX>()
+                                                                             : kWave * (int)sizeof(int);
+  constexpr int least = ssa + (SMAX <= 12 ? 0 : drawn_items<SMAX, RMAX>() * (int)sizeof(int));
   const int items = S * kWave * (int)sizeof(ItemWord<SMAX>);
   return S * kWave * (int)sizeof(int) + (items > least ? items : least);
 }
+
+// The LDS of a compute unit is handed out in granules of 1,280 bytes, of which
+// it has 128: twelve blocks of 16 species fit in ten granules each, and four
+// bytes more leave room for eleven.  (The occupancy query does not know: at 11
+// granules it says twelve, and the blocks that then wait for a place ran as a
+// last round of their own: 375,000 tets of 16 species, 20 molecules of each in a
+// tet, 334 us a window so, in ten granules 243.)
+constexpr int kLdsGranule = 1280, kLdsGranules = 128;
+template <int SMAX, int RMAX>
+constexpr int lds_blocks(int S) {
+  return kLdsGranules /
+         ((int)((sizeof(TileLds<SMAX, RMAX>) + tile_row_bytes<SMAX, RMAX>(S) + kLdsGranule - 1) / kLdsGranule));
+}
+static_assert(lds_blocks<4, 4>(4) >= 16 && lds_blocks<8, 8>(8) >= 16 && lds_blocks<12, 12>(12) >= 16 &&
+                  lds_blocks<16, 24>(16) >= 12 && lds_blocks<16, 32>(16) >= 12,
+              "room for the waves that the registers allow");
 
 // The largest of the GL lanes' values, on all of them (butterfly within rows of
 // 16 lanes).
@@ -912,6 +933,14 @@ window_main_kernel(const StepArgs A) {
   constexpr int kPackedCount = 1 << (8 * (int)sizeof(item_t) - 10);  // counts from here on do not fit an item
   item_t* const items = reinterpret_cast<item_t*>(tile_rows + A.S * kWave);
   int* const moved_n = reinterpret_cast<int*>(items);
+  // The post-reaction counts of changed items, from the last one of this space
+  // back.  Above 12 species they lie at the end of the items': that has a word
+  // for each (tet, species) pair, and a changed one is not in the list that
+  // fills it from its start (nor do the rows of the reaction operator, there
+  // meanwhile, reach it).
+  constexpr int kDrawn = TileLds<SMAX, RMAX>::kDrawn;
+  int* const npost = SMAX <= 12 ? &L.npost[SMAX <= 12 ? kDrawn - 1 : 0]
+                                : reinterpret_cast<int*>(tile_rows) + tile_row_bytes<SMAX, RMAX>(A.S) / (int)sizeof(int) - 1;
   // The first tile's counts are at the end of a chain of loads (arguments,
   // step and run, rows) that a block of two or three tiles feels: what of it
   // is known by now is read at once, a word of each cache line, so that later
@@ -1151,11 +1180,11 @@ window_main_kernel(const StepArgs A) {
         if (mine) {
 #pragma unroll
           for (int s = 0; s < SMAX; ++s) moved_n[rank * GL + s] = N[s];
-          L.npost[n_drawn + rank] = lane;  // space not yet in use
+          npost[-(n_drawn + rank)] = lane;  // space not yet in use
         }
         wave_sync();
         const bool run = c0 + grp < n_listed;
-        const int Lt = run ? L.npost[n_drawn + grp] : 0;
+        const int Lt = run ? npost[-(n_drawn + grp)] : 0;
         int Nj = run && j < SMAX ? moved_n[ln] : 0;
         const double nav_t = lane_read(nav, Lt);
         const int reg_t = __builtin_amdgcn_ds_bpermute(4 * Lt, reg);
@@ -1179,7 +1208,7 @@ window_main_kernel(const StepArgs A) {
         if (item) {
           const int at = n_drawn + (int)__popcll(bi & below);
           L.drawn[at] = (uint16_t)((Lt << 4) | j);
-          L.npost[at] = Nj;
+          npost[-at] = Nj;
           L.nbar[at] = (O + (double)Nj * (tau - t)) / tau;
         } else if (touched && Nj != 0) {
           atomicAdd(acc + (j * kWave + Lt), Nj);
@@ -1295,7 +1324,7 @@ window_main_kernel(const StepArgs A) {
             const uint32_t itw = at < n_drawn ? (uint32_t)L.drawn[at] : (uint32_t)items[at - n_drawn];
             Ln = (int)((itw >> 4) & 63);
             sp = (int)(itw & 15);
-            m = at < n_drawn ? L.npost[at] : (int)(itw >> 10);
+            m = at < n_drawn ? npost[-at] : (int)(itw >> 10);
             nb = at < n_drawn ? L.nbar[at] : 0.0;
           }
         } else if (valid) {
@@ -1457,6 +1486,7 @@ int window_resident(int S) {
     (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
     (void)hipOccupancyMaxActiveBlocksPerMultiprocessor(
         &per_cu, reinterpret_cast<const void*>(&window_main_kernel<SMAX, RMAX>), kWave, tile_row_bytes<SMAX, RMAX>(S));
+    per_cu = per_cu < lds_blocks<SMAX, RMAX>(S) ? per_cu : lds_blocks<SMAX, RMAX>(S);
     n = n_cu > 0 && per_cu > 0 ? n_cu * per_cu : 2048;
     known[S].store(n, std::memory_order_relaxed);
   }

@@ -54,7 +54,7 @@ typedef unsigned uint4_row __attribute__((ext_vector_type(4), aligned(4)));
 //
 // U loads of a lane at a time: four, or one where a block a CU then has every
 // tet.  There the adds of the loads past the end are what is felt (eight
-// accumulators, 128 adds a load): 1,296 and 15,288 tets of 16 species in eight
+// accumulators, 32 adds a load): 1,296 and 15,288 tets of 16 species in eight
 // regions 12.90 and 12.96 us a record with four, 12.31 and 12.58 with one.
 template <int NR, int U>
 __global__ __launch_bounds__(kRecThreads) void region_counts_kernel(
