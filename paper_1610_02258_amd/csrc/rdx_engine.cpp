@@ -507,8 +507,26 @@ rdx_status Engine::plan_steps(Run* r, int64_t n) {
 }
 
 namespace {
-// Fewest rounds of tiles `resident` blocks need, then the fewest blocks (a
-// multiple of the 8 XCDs) that still finish in that many rounds.
+// Tiles of the busiest SIMD when `grid` blocks walk n_tiles in static ranges.
+// An XCD has an eighth of both; its block j takes the tiles j, j + blocks, ...
+// and lands, in order, on SIMD j mod 128 of its 32 compute units.
+int64_t busiest_simd(int64_t n_tiles, int grid) {
+  constexpr int64_t kSimds = 128;
+  const int64_t tiles = (n_tiles + 7) / 8, blocks = std::max(1, grid / 8);
+  int64_t load = 0;
+  for (int64_t j = 0; j < blocks && j < tiles; j += kSimds) load += (tiles - j + blocks - 1) / blocks;
+  return load;
+}
+
+// Grid of static ranges: the fewest rounds of tiles that `resident` blocks
+// need, in the fewest blocks (a multiple of the 8 XCDs) for that many rounds;
+// more blocks than that where the busiest SIMD then has fewer tiles, the
+// fewest that do best.  7,500 tiles of 15 species at 3,072 resident blocks:
+// 2,504 blocks make three rounds, and 9 tiles for a SIMD with three of them;
+// at 2,752 the third has two rounds to go, 8 tiles: 331 and 270 us a window with
+// 20 molecules a species and tet, 77 and 71 with one.  At 8 species (4,096
+// resident) 4,578 tiles, 6 or 5 a SIMD, 130 and 109 us, 34 and 32; 15,000 tiles,
+// 16 or 15, 303 and 272.
 int rounds_grid(int64_t n_tiles, int resident) {
   resident = std::max(8, resident);
   if (n_tiles < 1) return 1;
@@ -516,6 +534,16 @@ int rounds_grid(int64_t n_tiles, int resident) {
   int g = (int)((n_tiles + rounds - 1) / rounds);
   if (g >= 8) g = (g + 7) & ~7;
   if (g > resident) g = resident & ~7;
+  if (rounds > 1) {
+    int64_t least = busiest_simd(n_tiles, g);
+    for (int more = g + 8; more <= resident; more += 8) {
+      const int64_t load = busiest_simd(n_tiles, more);
+      if (load < least) {
+        least = load;
+        g = more;
+      }
+    }
+  }
   return g > 0 ? g : 1;
 }
 }  // namespace
