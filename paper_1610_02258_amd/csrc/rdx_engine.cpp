@@ -574,13 +574,21 @@ static int64_t bucket_tiles(int64_t n) {
 // tiles differ in cost, and shorter ones are shared out better: up to 5/4 of
 // the resident blocks.  Calcium branch of 112,000 tets, events crowded in a
 // part of it (1.14 times the blocks at 32) 347 / 225 / 224 / 298 us.
+//
+// Without reactions a tile needs more items than half a wave's lanes: one
+// species takes 64 tets, two take 32 (60,000 tets, 20 molecules each: one
+// species 15.4 / 16.9 / 22.1 us at 64 / 32 / 16, two 20.8 / 18.1 / 22.2, three
+// 25.3 / 22.9 / 23.4; with events a shorter tile has fewer listed tets, and one
+// species with two events a tet takes 60.3 / 41.1 / 37.3).
 void Engine::cover(int64_t n_tiles_exact, const ExecShape& sh, StepArgs* a) const {
   const int resident = std::max(8, grid_resident(S_, R_) / std::max(1, sh.fast_grid_div));
   const int64_t tiles64 = max_runs_ > 1 ? bucket_tiles(n_tiles_exact) : n_tiles_exact;
   const bool claim = sh.tile_claim != 0;
   const int64_t most = claim ? (int64_t)resident * 5 / 4 : resident / 2;
   a->tile_shift = 6;
-  while (a->tile_shift > 4 && (tiles64 << (7 - a->tile_shift)) <= most) --a->tile_shift;
+  while (a->tile_shift > 4 && (tiles64 << (7 - a->tile_shift)) <= most &&
+         (R_ > 0 || (S_ << (a->tile_shift - 1)) > 32))
+    --a->tile_shift;
   const int64_t n_tiles = tiles64 << (6 - a->tile_shift);
   a->tile_claim = sh.tile_claim;
   // claimed tiles: every block the device holds, whatever the number of tiles
