@@ -210,10 +210,11 @@ def roofline(T: int, S: int, n_regions: int, windows: int, face_moves: int, kt: 
            "avg_launch_us": main_s * 1e6, "duration_source": source,
            "window": {"detect_us": det_s * 1e6, "main_us": main_s * 1e6,
                       "achieved_GBs": b / (main_s + det_s) / 1e9,
-                      "frac": b / (main_s + det_s) / 1e9 / HBM_PEAK_GBS},
-           "detect_kernel": {"avg_launch_us": det_s * 1e6,
-                             "bytes_per_launch": detect_kernel_bytes(T, S, n_regions),
-                             "achieved_GBs": detect_kernel_bytes(T, S, n_regions) / det_s / 1e9 if det_s else None}}
+                      "frac": b / (main_s + det_s) / 1e9 / HBM_PEAK_GBS}}
+    if det_s:  # a listing pass of its own
+        out["detect_kernel"] = {"avg_launch_us": det_s * 1e6,
+                                "bytes_per_launch": detect_kernel_bytes(T, S, n_regions),
+                                "achieved_GBs": detect_kernel_bytes(T, S, n_regions) / det_s / 1e9}
     rp = rocprof_durations(workload)
     if rp:
         out["rocprof"] = {"main_us": rp["main_us"], "detect_us": rp["detect_us"],

@@ -171,11 +171,6 @@ size_t Engine::run_bytes(const HostInstance& I) {
   return b;
 }
 
-size_t Engine::worklist_bytes_per_tet(int S) {
-  (void)S;
-  return 5;
-}
-
 void Engine::fence(hipStream_t stream) {
   for (auto& f : fences_)
     if (f.first == stream) {
@@ -572,8 +567,13 @@ static int64_t bucket_tiles(int64_t n) {
 // 60,000 tets (half of the blocks at 32) 26.8 / 22.9 / 24.0 / 36.3 us,
 // 480,000 tets at ten times the density 74 / 89 / 123 / 185 us.  Claimed
 // tiles differ in cost, and shorter ones are shared out better: up to 5/4 of
-// the resident blocks.  Calcium branch of 112,000 tets, events crowded in a
-// part of it (1.14 times the blocks at 32) 347 / 225 / 224 / 298 us.
+// the resident blocks.  Calcium branch, events crowded in a part of it, 64 / 32
+// / 16 tets: 60,000 tets (0.61 and 1.22 times the blocks at 32 and 16) 427 / 258
+// / 197 us, 112,000 (1.14, 2.27) 250 / 171 / 179, 160,000 (1.62) 195 / 172 / 200,
+// 249,000 (2.53) 151 / 154 / 207.  Beyond the line the crowded loads still gain
+// a little and the even ones lose: 150,000 tets of 16 species (1.53), 20
+// molecules of each in a tet 124 / 120 us, nearly empty 18.8 / 23.9; 243,000 of 8
+// species (1.85) 85 / 97.
 //
 // Without reactions a tile needs more items than half a wave's lanes: one
 // species takes 64 tets, two take 32 (60,000 tets, 20 molecules each: one

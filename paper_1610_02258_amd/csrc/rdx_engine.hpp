@@ -104,9 +104,9 @@ class Engine {
   // Device bytes of one run's state (counts, mesh arrays, tables, tallies).
   static size_t run_bytes(const HostInstance& I);
   // Bytes a server's budget sets aside per tet of capacity beside the runs'
-  // state.  More than the tile map takes (8 per tile of 64 tets); what a
-  // budget admits rests on it.
-  static size_t worklist_bytes_per_tet(int S);
+  // state: more than the tile map takes (8 per 64 tets), and kept so, because
+  // which budgets, requests and numbers of runs are admitted rests on it.
+  static constexpr size_t kBudgetBytesPerTet = 5;
 
   // `proto` fixes the shared species/reaction structure.  arena_bytes holds
   // the runs' state; max_runs and max_tets bound what may be resident.
@@ -171,7 +171,7 @@ class Engine {
   ExecShape shape() const { return shape_; }
   bool tuning() const { return tuning_; }
 
-  // Per-kernel timing (plain launches, three events per window).
+  // Per-kernel timing (plain launches, two events per window).
   void set_timing(bool on) { timing_ = on; }
   rdx_status kernel_times(rdx_kernel_times* out, bool reset);
 
@@ -273,8 +273,7 @@ class Engine {
   double main_ms_ = 0.0;
 };
 
-// DevModel of a validated instance (packed reaction entries, net changes,
-// dependency masks).
+// DevModel of a validated instance (packed reaction entries, net changes).
 DevModel make_dev_model(const HostInstance& I);
 
 }  // namespace rdx

@@ -173,7 +173,7 @@ __constant__ constexpr ReciprocalTable kRecip{};
 // test.  Running past the end is harmless: the cdf does not fall (terms past
 // k = c are zero), so the answer is the number of cdf values that u reaches,
 // counted term by term and capped at c.  Against single steps: a window of the
-// 112k-tet dendrite (counts near 1000, about 100 terms a search) 915 -> 600 us,
+// 112k-tet dendrite (counts near 1000, about 100 terms a search) 915 -> 608 us,
 // of the 1M-tet one (counts near 110) 258 -> 247 us.
 constexpr int kSearchSteps = 8;
 static_assert(1000 % kSearchSteps == 0, "a pass never reads past the reciprocals");
@@ -265,9 +265,9 @@ __device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
 }
 
 // -------------------------------------------------------- window kernel ----
-// A window of a batch is one launch of window_main_kernel: persistent blocks of one
-// wave (64 lanes), one lane per tet, a tile of 64, 32 or 16 tets at a time (a
-// tile belongs to one run).  Per tile:
+// A window of a batch is one launch of window_main_kernel: persistent blocks of
+// one wave (64 lanes), one lane per tet, a tile of 64, 32 or 16 tets at a time
+// (a tile belongs to one run).  Per tile:
 //
 // Listing: a0 from regrouped coefficients and the tet's first SSA uniform.
 // A tet whose first event may fall inside the window is listed.
@@ -277,22 +277,25 @@ __device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
 // many at a time as the wave has groups.
 //
 // Diffusion items: every (tet, species) pair with something to sample becomes
-// an item; they are packed into LDS and sampled in rounds of 64, one per lane.  Moves into the tile's own tets accumulate in LDS and are
-// flushed once, coalesced; the rest are integer atomics into the next count
-// buffer.
+// an item; they are packed into LDS and sampled in rounds of 64, one per lane.
+// Moves into the tile's own tets accumulate in LDS and are flushed once,
+// coalesced; the rest are integer atomics into the next count buffer.
 //
 // What the one launch replaces: a listing launch over all tiles, which wrote
 // queues of listed tets, and event blocks beside the diffusion blocks, which
 // read the tets again and ran them in chunks.  The chain queue counters ->
-// queue -> worklist -> counts took 7 us before a chunk's first propensity, a
+// queue -> listed tets -> counts took 7 us before a chunk's first propensity, a
 // chunk could hold one run only, and the event blocks ended last wherever
 // tiles are few or runs small.  Here the tet is read once, listed, stepped and
 // diffused by the wave that holds it.  Per window, two launches against one:
 // 480,000 tets, 10 species, 2 molecules a tet 42.4 -> 35.1 us; a million
 // molecules in 60,000 tets of it 47.2 -> 21.0 us; 112,000 tets of the calcium
-// model with events crowded in one region 970 -> 220 us (by the binomial
+// model with events crowded in one region 915 -> 220 us (by the binomial
 // search alone 608); a million tets of it 258 -> 223 us; 48 runs of 200 to
-// 1,500 tets 60 -> 19 us.
+// 1,500 tets 60 -> 19 us.  Also where every tet has events (4 molecules a
+// species, 0.9 and 15 events a tet and window): 480,000 tets of 3 species 266 ->
+// 133 and 1,119 -> 707 us, of 10 species 654 -> 323 and 2,512 -> 1,810, of 16
+// species 2,433 -> 552 and 17,107 -> 3,789.
 //
 // What bounds a tile: the chain of a lone wave (a load, the propensities and a
 // Philox call, the item list, the items' draws), 9 us where tets hold two
@@ -302,10 +305,11 @@ __device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
 // waves per SIMD: four for up to 12 species, three above.
 constexpr int kWave = 64;
 
-// Tables the window kernels only read -- the run table, the tile map, the
-// reaction tables, the step base and tile count -- are read through the
-// constant address space: nothing writes them while a kernel runs, and a
-// uniform address can then be served by a scalar load, whose wait does not
+// Tables the window kernel only reads -- the run table, the tile map, the
+// reaction tables, the step word and tile count -- are read through the
+// constant address space: nothing writes what is read while a kernel runs (of
+// the two step words it writes the other one, which the next kernel reads), and
+// a uniform address can then be served by a scalar load, whose wait does not
 // hold up the vector loads in flight.
 template <typename T>
 using cptr = const __attribute__((address_space(4))) T*;

@@ -115,7 +115,8 @@ constexpr int64_t kResetChunk = 16384;  // elements per chunk
 hipError_t launch_reset_chunks(const ResetChunk* chunks, int64_t n_chunks, hipStream_t stream);
 
 // Recording (rdx_record.hip): out [n_regions * S] = per-region sums of the
-// counts [S][T]; region may be null when n_regions == 1.  scratch is a device
+// counts [S][T]; region may be null when n_regions == 1, else it is aligned to
+// four bytes (labels are read as 32-bit words).  scratch is a device
 // array of kRegionScratchBytes for per-block partial sums (calls sharing it
 // must be ordered on one stream).
 constexpr size_t kRegionScratchBytes = 4096 * 8 * 8;

@@ -343,21 +343,19 @@ rdx_status rdx_server_create(const rdx_model* structure, const rdx_server_option
   (void)hipGetDevice(&s->device);
   // default: at most 1024 resident requests, and the tiles their last tets pad
   // at most an eighth of the budget
-  const size_t wl_tet0 = Engine::worklist_bytes_per_tet(proto.S);
+  constexpr size_t per_cap = Engine::kBudgetBytesPerTet;
   const int max_runs = opts->max_runs
                            ? opts->max_runs
-                           : (int)std::max<size_t>(1, std::min<size_t>(1024, opts->hbm_budget_bytes / (512 * wl_tet0)));
+                           : (int)std::max<size_t>(1, std::min<size_t>(1024, opts->hbm_budget_bytes / (512 * per_cap)));
   s->tick_windows = opts->tick_windows ? opts->tick_windows : 8;
-  // the budget holds the tile map (per tet of capacity, plus a padded tile
+  // the budget holds what is set aside per tet of capacity (with 64 tets more
   // per resident run) and the runs' state
-  const size_t wl_tet = Engine::worklist_bytes_per_tet(proto.S);
-  const size_t pad = 64 * (size_t)max_runs * wl_tet;
+  const size_t pad = 64 * (size_t)max_runs * per_cap;
   if (opts->hbm_budget_bytes < 2 * pad) return set_error(RDX_EINVAL, "budget too small for max_runs");
-  const size_t per_tet = wl_tet + 8 * (size_t)proto.S + 57;
+  const size_t per_tet = per_cap + 8 * (size_t)proto.S + 57;
   int64_t cap = (int64_t)((opts->hbm_budget_bytes - pad) / per_tet);
   cap = std::min<int64_t>(cap, INT32_MAX / 256);
-  const size_t wl = (size_t)cap * wl_tet + pad;
-  const size_t arena = opts->hbm_budget_bytes - wl;
+  const size_t arena = opts->hbm_budget_bytes - ((size_t)cap * per_cap + pad);
   s->capacity_tets = cap;
   st = s->eng.init(proto, arena, max_runs, cap);
   if (st != RDX_OK) return st;
