@@ -301,7 +301,7 @@ __device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
 // Philox call, the item list, the items' draws), 9 us where tets hold two
 // molecules against 0.4 us of memory traffic at the copy rate, and VALU issue
 // where they hold hundreds (69% of the issue slots at the million-tet calcium
-// dendrite, 6,219 instructions a tile; 33% at two molecules, 1,129).  Hence
+// dendrite, 6,200 instructions a tile; 32% at two molecules, 1,119).  Hence
 // waves per SIMD: four for up to 12 species, three above.
 constexpr int kWave = 64;
 
